@@ -3,9 +3,10 @@
 // operands, FP32 accumulation), plus the gradient reduction and the Adam
 // update (Kingma & Ba 2015).
 //
-// Work split: a wave owns a tile of 16 samples and carries it through all
-// three layers (and back); a work-group of four waves shares one bfloat16 copy
-// of the weights in LDS.  Products over the 64 hidden units (forward layers 2
+// Work split: a work-group of four waves owns a tile of 16 samples; wave w
+// computes the hidden units [16 w, 16 w + 16) of every layer (forward and
+// back) and those units' weight gradients, and the activations are exchanged
+// through LDS.  Products over the 64 hidden units (forward layers 2
 // and 3, the error back-propagated into layer 1) are sums of 16 x 16 x 32
 // tiles (v_mfma_f32_16x16x32_bf16); products over 16 (the padded inputs and
 // outputs, and the weight gradients over the tile's 16 samples) take the
@@ -24,8 +25,6 @@ typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int MLP_WAVES = 4;  // tiles of 16 samples per work-group
-
 __device__ __forceinline__ uint16_t to_bf16(float v) {  // round to nearest even (finite inputs)
     uint32_t u = __float_as_uint(v);
     u += 0x7FFFu + ((u >> 16) & 1u);
@@ -33,257 +32,299 @@ __device__ __forceinline__ uint16_t to_bf16(float v) {  // round to nearest even
 }
 __device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-// acc += A * B for 16 x 16 tiles given by element accessors A(m, k), B(k, n)
-// returning bfloat16 bits.  Lane l supplies A[l % 16][4 (l / 16) + j] and
-// B[4 (l / 16) + j][l % 16], j = 0..3, and receives D[4 (l / 16) + j][l % 16].
-template <class FA, class FB>
-__device__ __forceinline__ f32x4 mma16(FA A, FB B, f32x4 acc, int lane) {
-    const int r = lane & 15, g = lane >> 4;
-    bf16x4 a, b;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        a[j] = (short)A(r, 4 * g + j);
-        b[j] = (short)B(4 * g + j, r);
-    }
+// Operand layouts of the two products.  16 x 16 x 16: lane l (r = l % 16,
+// g = l / 16) supplies A[r][4 g + j] and B[4 g + j][r], j = 0..3.
+// 16 x 16 x 32: A[r][8 g + j] and B[8 g + j][r], j = 0..7 (A and B take the
+// same K order, so the sum pairs A[m][k] with B[k][n] whatever K order the
+// unit uses).  Both give D[4 g + j][r].  A result rounded to bfloat16 is
+// therefore, as it stands, an operand of a product over its rows (the 16
+// samples), which is what every weight gradient is.
+__device__ __forceinline__ f32x4 mma16(bf16x4 a, bf16x4 b, f32x4 acc) {
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
 }
-
-// The same for a K = 32 slice: lane l supplies A[l % 16][8 (l / 16) + j] and
-// B[8 (l / 16) + j][l % 16], j = 0..7; D as above.  A and B take the same K
-// order, so the sum pairs A[m][k] with B[k][n] whatever K order the unit uses.
-template <class FA, class FB>
-__device__ __forceinline__ f32x4 mma32(FA A, FB B, f32x4 acc, int lane) {
-    const int r = lane & 15, g = lane >> 4;
-    bf16x8 a, b;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        a[j] = __builtin_bit_cast(__bf16, (uint16_t)A(r, 8 * g + j));
-        b[j] = __builtin_bit_cast(__bf16, (uint16_t)B(8 * g + j, r));
-    }
+__device__ __forceinline__ f32x4 mma32(bf16x8 a, bf16x8 b, f32x4 acc) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
 }
 
-struct MlpShm {
-    uint16_t w1[MLP_H][16];   // W1 with the 8 inputs padded to 16
-    uint16_t w2[MLP_H][MLP_H];
-    uint16_t w3[16][MLP_H];   // W3 with the 6 outputs padded to 16
-    struct Wave {
-        uint16_t x[16][16];
-        uint16_t h1[16][MLP_H], h2[16][MLP_H];
-        uint16_t d3[16][16], d2[16][MLP_H], d1[16][MLP_H];
-        float e[16][MLP_H];   // FP32 error terms of the current layer (bias gradients)
-    } w[MLP_WAVES];
+// Four consecutive floats of a caller's array (4-byte aligned only).
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ f32x4u ld4(const float* p) { return *reinterpret_cast<const f32x4u*>(p); }
+
+__device__ __forceinline__ bf16x4 pack4(float v0, float v1, float v2, float v3) {
+    return bf16x4{(short)to_bf16(v0), (short)to_bf16(v1), (short)to_bf16(v2), (short)to_bf16(v3)};
+}
+__device__ __forceinline__ bf16x8 pack8(f32x4u lo, f32x4u hi) {
+    bf16x8 v;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        v[j] = __builtin_bit_cast(__bf16, to_bf16(lo[j]));
+        v[4 + j] = __builtin_bit_cast(__bf16, to_bf16(hi[j]));
+    }
+    return v;
+}
+
+constexpr int MLP_ROW = MLP_H + 8;  // padded row of 64 units: 16-byte aligned, 4 rows apart on other banks
+struct alignas(16) MlpShm {
+    uint16_t h1[16][MLP_ROW], h2[16][MLP_ROW], d2[16][MLP_ROW];  // [sample][unit]
+    bf16x4 h1p[4][64];   // h1 as results lie: block of 16 units, lane -> 4 samples of one unit
+    uint16_t d3[4][16][20];  // [wave][sample][output], each wave's own copy
 };
+
+// Sums e over the 16 samples in order (lane (r, g) holds samples 4 g + j of
+// unit r); lanes with g = 3 return the total.  The terms are added as rounded
+// (contraction off: e is a product in the caller).
+__device__ __forceinline__ float sum_samples(const float (&e)[4], int r) {
+#pragma clang fp contract(off)
+    float s = 0.f, t = 0.f;
+#pragma unroll
+    for (int gg = 0; gg < 4; ++gg) {
+        t = s;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) t += e[j];
+        if (gg < 3) s = __shfl(t, 16 * gg + r);
+    }
+    return t;
+}
 
 // mode 0: outputs for n samples -> out (n x 6).  mode 1: loss and gradient of
 // the mean squared error against Y, scaled so that the tiles' partial
 // gradients sum to the gradient of L = scale / 2 * sum (y - Y)^2; partial of
 // tile t at G + t * MLP_NP, its sum of squared errors at Lpart[t].
-__global__ __launch_bounds__(64 * MLP_WAVES) void k_mlp(MlpArgs a) {
+//
+// Bound by latency: a tile is 68 small matrix products, so what counts is
+// the length of the chain and how many compute units share a mini-batch.  Each
+// lane loads the weights of its wave's units straight into operand
+// registers, all loads in flight at once (no LDS copy of the weights, whose
+// staging loops were most of the kernel's time), and a tile has a
+// work-group, so a mini-batch of 256 runs on 16 compute units instead of 4:
+// 6.4 us (22.2 us with four tiles to a work-group and weights staged in LDS);
+// 2048 samples forward and back 9.5 us, forward alone 6.6 us (22 and 15).
+template <int MODE>
+__global__ __launch_bounds__(256) void k_mlp(MlpArgs a) {
     __shared__ MlpShm sh;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, r = lane & 15, g = lane >> 4;
+    const int base = blockIdx.x * 16, unit = 16 * w + r;
     const float* P = a.P;
-    for (int k = tid; k < MLP_H * 16; k += blockDim.x) {
-        const int o = k >> 4, i = k & 15;
-        sh.w1[o][i] = i < MLP_IN ? to_bf16(P[MLP_OW1 + o * MLP_IN + i]) : 0;
+    // weights, inputs and targets
+    f32x4u x4 = {0, 0, 0, 0}, w1 = {0, 0, 0, 0};
+    if (g < 2) {
+        w1 = ld4(P + MLP_OW1 + unit * MLP_IN + 4 * g);
+        if (base + r < a.n) x4 = ld4(a.X + (long long)(base + r) * MLP_IN + 4 * g);
     }
-    for (int k = tid; k < MLP_H * MLP_H; k += blockDim.x) sh.w2[k >> 6][k & 63] = to_bf16(P[MLP_OW2 + k]);
-    for (int k = tid; k < 16 * MLP_H; k += blockDim.x) {
-        const int o = k >> 6;
-        sh.w3[o][k & 63] = o < MLP_OUT ? to_bf16(P[MLP_OW3 + k]) : 0;
+    f32x4u w2[4], w3[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int col = 32 * (k >> 1) + 8 * g + 4 * (k & 1);
+        w2[k] = ld4(P + MLP_OW2 + unit * MLP_H + col);
+        w3[k] = f32x4u{0, 0, 0, 0};
+        if (r < MLP_OUT) w3[k] = ld4(P + MLP_OW3 + r * MLP_H + col);
     }
-    MlpShm::Wave& W = sh.w[wv];
-    const int tile = blockIdx.x * MLP_WAVES + wv;
-    const int base = tile * 16;
-    for (int k = lane; k < 256; k += 64) {
-        const int m = k >> 4, i = k & 15;
-        W.x[m][i] = (i < MLP_IN && base + m < a.n) ? to_bf16(a.X[(long long)(base + m) * MLP_IN + i]) : 0;
+    const float b1 = P[MLP_OB1 + unit], b2 = P[MLP_OB2 + unit], b3 = r < MLP_OUT ? P[MLP_OB3 + r] : 0.f;
+    float xt[4], yt[4], w3t[4], w2t[2][8];  // mode 1: targets, and weights and inputs as the backward products take them
+    if constexpr (MODE == 1) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int m = base + 4 * g + j;
+            xt[j] = r < MLP_IN && m < a.n ? a.X[(long long)m * MLP_IN + r] : 0.f;
+            yt[j] = r < MLP_OUT && m < a.n ? a.Y[(long long)m * MLP_OUT + r] : 0.f;
+            w3t[j] = 4 * g + j < MLP_OUT ? P[MLP_OW3 + (4 * g + j) * MLP_H + unit] : 0.f;
+        }
+#pragma unroll
+        for (int ot = 0; ot < 2; ++ot)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) w2t[ot][j] = P[MLP_OW2 + (32 * ot + 8 * g + j) * MLP_H + unit];
     }
-    __syncthreads();
-    // every wave runs every phase (a tile past the end computes on zeros and
-    // writes nothing), so the work-group barriers below are reached by all
-    const bool live = base < a.n;
-    const int r = lane & 15, g = lane >> 4;
+    const f32x4 zero = {0, 0, 0, 0};
 
     // forward
+    f32x4 acc = mma16(pack4(x4[0], x4[1], x4[2], x4[3]), pack4(w1[0], w1[1], w1[2], w1[3]), zero);
+    uint16_t h1[4], h2[4];
 #pragma unroll
-    for (int ot = 0; ot < 4; ++ot) {
-        f32x4 acc = {0, 0, 0, 0};
-        acc = mma16([&](int m, int k) { return W.x[m][k]; }, [&](int k, int n) { return sh.w1[16 * ot + n][k]; },
-                    acc, lane);
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            W.h1[4 * g + j][16 * ot + r] = to_bf16(tanhf(acc[j] + P[MLP_OB1 + 16 * ot + r]));
+    for (int j = 0; j < 4; ++j) {
+        h1[j] = to_bf16(tanhf(acc[j] + b1));
+        sh.h1[4 * g + j][unit] = h1[j];
     }
+    if constexpr (MODE == 1) sh.h1p[w][lane] = bf16x4{(short)h1[0], (short)h1[1], (short)h1[2], (short)h1[3]};
     __syncthreads();
-#pragma unroll
-    for (int ot = 0; ot < 4; ++ot) {
-        f32x4 acc = {0, 0, 0, 0};
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-            acc = mma32([&](int m, int k) { return W.h1[m][32 * kt + k]; },
-                        [&](int k, int n) { return sh.w2[16 * ot + n][32 * kt + k]; }, acc, lane);
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            W.h2[4 * g + j][16 * ot + r] = to_bf16(tanhf(acc[j] + P[MLP_OB2 + 16 * ot + r]));
-    }
-    __syncthreads();
-    f32x4 y = {0, 0, 0, 0};
+    acc = zero;
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt)
-        y = mma32([&](int m, int k) { return W.h2[m][32 * kt + k]; },
-                  [&](int k, int n) { return sh.w3[n][32 * kt + k]; }, y, lane);
-    if (a.mode == 0) {
-        if (r < MLP_OUT)
+        acc = mma32(*reinterpret_cast<const bf16x8*>(&sh.h1[r][32 * kt + 8 * g]), pack8(w2[2 * kt], w2[2 * kt + 1]),
+                    acc);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        h2[j] = to_bf16(tanhf(acc[j] + b2));
+        sh.h2[4 * g + j][unit] = h2[j];
+    }
+    __syncthreads();
+    f32x4 y = zero;  // every wave: the next product needs all of it
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt)
+        y = mma32(*reinterpret_cast<const bf16x8*>(&sh.h2[r][32 * kt + 8 * g]), pack8(w3[2 * kt], w3[2 * kt + 1]), y);
+    if constexpr (MODE == 0) {
+        if (w == 0 && r < MLP_OUT)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const int m = 4 * g + j;
-                if (live && base + m < a.n) a.out[(long long)(base + m) * MLP_OUT + r] = y[j] + P[MLP_OB3 + r];
+                const int m = base + 4 * g + j;
+                if (m < a.n) a.out[(long long)m * MLP_OUT + r] = y[j] + b3;
             }
         return;
     }
 
-    // backward: e3 = dL/dy.  Tiles past the end write nothing (G is only
-    // valid for tiles that hold samples)
-    float* G = live ? a.G + (long long)tile * MLP_NP : nullptr;
-    float sq = 0.f;
+    // backward: e3 = dL/dy
+    float* G = a.G + (long long)blockIdx.x * MLP_NP;
+    float sq = 0.f, e[4];
+    bf16x4 d3;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const int m = 4 * g + j;
-        float e = 0.f;
-        if (r < MLP_OUT && base + m < a.n) {
-            const float d = y[j] + P[MLP_OB3 + r] - a.Y[(long long)(base + m) * MLP_OUT + r];
+        const int m = base + 4 * g + j;
+        e[j] = 0.f;
+        if (r < MLP_OUT && m < a.n) {
+            const float d = y[j] + b3 - yt[j];
             sq += d * d;
-            e = a.scale * d;
+            e[j] = a.scale * d;
         }
-        W.e[m][r] = e;
-        W.d3[m][r] = to_bf16(e);
+        d3[j] = (short)to_bf16(e[j]);
+        sh.d3[w][4 * g + j][r] = (uint16_t)d3[j];
     }
-    __syncthreads();
-    // squared error of the tile (lanes hold disjoint entries)
-    for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
-    if (live && lane == 0) a.Lpart[tile] = sq;
-    if (live && lane < MLP_OUT) {
-        float s = 0.f;
-        for (int m = 0; m < 16; ++m) s += W.e[m][lane];
-        G[MLP_OB3 + lane] = s;
+    if (w == 0) {
+        // squared error of the tile (lanes hold disjoint entries)
+        for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
+        if (lane == 0) a.Lpart[blockIdx.x] = sq;
+        const float s = sum_samples(e, r);
+        if (g == 3 && r < MLP_OUT) G[MLP_OB3 + r] = s;
     }
     // dW3[n][k] = sum_m e3[m][n] h2[m][k]
+    const bf16x4 h2v = {(short)h2[0], (short)h2[1], (short)h2[2], (short)h2[3]};
+    acc = mma16(d3, h2v, zero);
 #pragma unroll
-    for (int kt = 0; kt < 4; ++kt) {
-        f32x4 acc = {0, 0, 0, 0};
-        acc = mma16([&](int n, int m) { return W.d3[m][n]; }, [&](int m, int k) { return W.h2[m][16 * kt + k]; },
-                    acc, lane);
+    for (int j = 0; j < 4; ++j)
+        if (4 * g + j < MLP_OUT) G[MLP_OW3 + (4 * g + j) * MLP_H + unit] = acc[j];
+    // e2 = (e3 W3) * (1 - h2^2); d3 comes back in another layout through this
+    // wave's own part of LDS, after its own writes
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    acc = mma16(*reinterpret_cast<const bf16x4*>(&sh.d3[w][r][4 * g]), pack4(w3t[0], w3t[1], w3t[2], w3t[3]), zero);
+    bf16x4 d2;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (live && 4 * g + j < MLP_OUT) G[MLP_OW3 + (4 * g + j) * MLP_H + 16 * kt + r] = acc[j];
-    }
-    // e2 = (e3 W3) * (1 - h2^2)
-#pragma unroll
-    for (int kt = 0; kt < 4; ++kt) {
-        f32x4 acc = {0, 0, 0, 0};
-        acc = mma16([&](int m, int n) { return W.d3[m][n]; }, [&](int n, int k) { return sh.w3[n][16 * kt + k]; },
-                    acc, lane);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int m = 4 * g + j, k = 16 * kt + r;
-            const float h = from_bf16(W.h2[m][k]);
-            const float e = acc[j] * (1.f - h * h);
-            W.e[m][k] = e;
-            W.d2[m][k] = to_bf16(e);
-        }
+    for (int j = 0; j < 4; ++j) {
+        const float h = from_bf16(h2[j]);
+        e[j] = acc[j] * (1.f - h * h);
+        d2[j] = (short)to_bf16(e[j]);
+        sh.d2[4 * g + j][unit] = (uint16_t)d2[j];
     }
     __syncthreads();
-    if (live) {
-        float s = 0.f;
-        for (int m = 0; m < 16; ++m) s += W.e[m][lane];
-        G[MLP_OB2 + lane] = s;
+    // e1 = (e2 W2) * (1 - h1^2)
+    acc = zero;
+#pragma unroll
+    for (int ot = 0; ot < 2; ++ot) {
+        bf16x8 b;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) b[j] = __builtin_bit_cast(__bf16, to_bf16(w2t[ot][j]));
+        acc = mma32(*reinterpret_cast<const bf16x8*>(&sh.d2[r][32 * ot + 8 * g]), b, acc);
     }
     // dW2[o][k] = sum_m e2[m][o] h1[m][k]
 #pragma unroll
-    for (int ot = 0; ot < 4; ++ot)
-#pragma unroll
-        for (int kt = 0; kt < 4; ++kt) {
-            f32x4 acc = {0, 0, 0, 0};
-            acc = mma16([&](int o, int m) { return W.d2[m][16 * ot + o]; },
-                        [&](int m, int k) { return W.h1[m][16 * kt + k]; }, acc, lane);
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (live) G[MLP_OW2 + (16 * ot + 4 * g + j) * MLP_H + 16 * kt + r] = acc[j];
-        }
-    // e1 = (e2 W2) * (1 - h1^2)
-    __syncthreads();
-#pragma unroll
     for (int kt = 0; kt < 4; ++kt) {
-        f32x4 acc = {0, 0, 0, 0};
+        const f32x4 v = mma16(d2, sh.h1p[kt][lane], zero);
 #pragma unroll
-        for (int ot = 0; ot < 2; ++ot)
-            acc = mma32([&](int m, int o) { return W.d2[m][32 * ot + o]; },
-                        [&](int o, int k) { return sh.w2[32 * ot + o][16 * kt + k]; }, acc, lane);
+        for (int j = 0; j < 4; ++j) G[MLP_OW2 + (16 * w + 4 * g + j) * MLP_H + 16 * kt + r] = v[j];
+    }
+    float s = sum_samples(e, r);
+    if (g == 3) G[MLP_OB2 + unit] = s;
+    bf16x4 d1;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int m = 4 * g + j, k = 16 * kt + r;
-            const float h = from_bf16(W.h1[m][k]);
-            const float e = acc[j] * (1.f - h * h);
-            W.e[m][k] = e;
-            W.d1[m][k] = to_bf16(e);
-        }
+    for (int j = 0; j < 4; ++j) {
+        const float h = from_bf16(h1[j]);
+        e[j] = acc[j] * (1.f - h * h);
+        d1[j] = (short)to_bf16(e[j]);
     }
-    __syncthreads();
-    if (live) {
-        float s = 0.f;
-        for (int m = 0; m < 16; ++m) s += W.e[m][lane];
-        G[MLP_OB1 + lane] = s;
-    }
+    s = sum_samples(e, r);
+    if (g == 3) G[MLP_OB1 + unit] = s;
     // dW1[o][i] = sum_m e1[m][o] x[m][i]
+    acc = mma16(d1, pack4(xt[0], xt[1], xt[2], xt[3]), zero);
+    if (r < MLP_IN)
 #pragma unroll
-    for (int ot = 0; ot < 4; ++ot) {
-        f32x4 acc = {0, 0, 0, 0};
-        acc = mma16([&](int o, int m) { return W.d1[m][16 * ot + o]; }, [&](int m, int i) { return W.x[m][i]; },
-                    acc, lane);
-        if (live && r < MLP_IN)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) G[MLP_OW1 + (16 * ot + 4 * g + j) * MLP_IN + r] = acc[j];
-    }
+        for (int j = 0; j < 4; ++j) G[MLP_OW1 + (16 * w + 4 * g + j) * MLP_IN + r] = acc[j];
 }
 
 // One thread per parameter: sum of the tiles' partial gradients in tile
 // order; mode 0 applies Adam (c1 = 1 / (1 - beta1^t), c2 = 1 / (1 - beta2^t)),
-// mode 1 writes the sum to gsum.  Thread 0 also adds the tiles' squared
-// errors to *loss_acc, or writes their sum over loss_div to *loss_out.
-__global__ __launch_bounds__(256) void k_mlp_reduce(MlpReduceArgs a) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p == 0 && (a.loss_acc || a.loss_out)) {
+// mode 1 writes the sum to gsum.  The last work-group also sums the tiles'
+// squared errors, adding to *loss_acc (or setting it, loss_first) or writing
+// the sum over loss_div to *loss_out.
+// Bound by latency: RED_LOADS loads of a thread are in flight together (the
+// sums stay in tile order), and work-groups of one wave spread the 5126
+// parameters over 81 compute units: 2.7 us for 16 tiles, 6.5 us for 128 (one
+// load at a time on 21 work-groups of 256: 6.1 and 35.8 us).
+constexpr int RED_BLOCK = 64, RED_LOADS = 32;
+__global__ __launch_bounds__(RED_BLOCK) void k_mlp_reduce(MlpReduceArgs a) {
+    const int lane = threadIdx.x;
+    if (blockIdx.x == gridDim.x - 1) {
+        if (!a.loss_acc && !a.loss_out) return;
         double s = 0.0;
-        for (int t = 0; t < a.ntiles; ++t) s += (double)a.Lpart[t];
-        if (a.loss_acc) *a.loss_acc += s;
-        if (a.loss_out) *a.loss_out = (float)(s / a.loss_div);
+        for (int t0 = 0; t0 < a.ntiles; t0 += RED_BLOCK) {
+            const float v = t0 + lane < a.ntiles ? a.Lpart[t0 + lane] : 0.f;
+            const int cnt = min(RED_BLOCK, a.ntiles - t0);
+            for (int k = 0; k < cnt; ++k) s += (double)__shfl(v, k);
+        }
+        if (lane == 0) {
+            if (a.loss_acc) *a.loss_acc = a.loss_first ? s : *a.loss_acc + s;
+            if (a.loss_out) *a.loss_out = (float)(s / a.loss_div);
+        }
+        return;
     }
+    const int p = blockIdx.x * RED_BLOCK + lane;
     if (p >= MLP_NP) return;
+    float m0 = 0.f, v0 = 0.f, p0 = 0.f;
+    if (a.mode == 0) {
+        m0 = a.M[p];
+        v0 = a.V[p];
+        p0 = a.P[p];
+    }
     float gsum = 0.f;
-    for (int t = 0; t < a.ntiles; ++t) gsum += a.G[(long long)t * MLP_NP + p];
+    const float* G = a.G + p;
+    int t0 = 0;
+    for (; t0 + RED_LOADS <= a.ntiles; t0 += RED_LOADS) {
+        float v[RED_LOADS];
+#pragma unroll
+        for (int k = 0; k < RED_LOADS; ++k) v[k] = G[(long long)(t0 + k) * MLP_NP];
+#pragma unroll
+        for (int k = 0; k < RED_LOADS; ++k) gsum += v[k];
+    }
+    for (; t0 < a.ntiles; t0 += 16) {
+        float v[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = G[(long long)min(t0 + k, a.ntiles - 1) * MLP_NP];
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            if (t0 + k < a.ntiles) gsum += v[k];
+    }
     if (a.mode == 1) {
         a.gsum[p] = gsum;
         return;
     }
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-    const float m = b1 * a.M[p] + (1.f - b1) * gsum;
-    const float v = b2 * a.V[p] + (1.f - b2) * gsum * gsum;
+    const float m = b1 * m0 + (1.f - b1) * gsum;
+    const float v = b2 * v0 + (1.f - b2) * gsum * gsum;
     a.M[p] = m;
     a.V[p] = v;
-    a.P[p] -= a.lr * (m * a.c1) / (sqrtf(v * a.c2) + eps);
+    a.P[p] = p0 - a.lr * (m * a.c1) / (sqrtf(v * a.c2) + eps);
 }
 
 hipError_t launch_mlp(const MlpArgs& a, hipStream_t st) {
     if (a.n <= 0) return hipSuccess;
     const int tiles = (a.n + 15) / 16;
-    const int blocks = (tiles + MLP_WAVES - 1) / MLP_WAVES;
-    hipLaunchKernelGGL(k_mlp, dim3(blocks), dim3(64 * MLP_WAVES), 0, st, a);
+    if (a.mode == 0)
+        hipLaunchKernelGGL(k_mlp<0>, dim3(tiles), dim3(256), 0, st, a);
+    else
+        hipLaunchKernelGGL(k_mlp<1>, dim3(tiles), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
 hipError_t launch_mlp_reduce(const MlpReduceArgs& a, hipStream_t st) {
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((MLP_NP + 255) / 256), dim3(256), 0, st, a);
+    // the parameters, and one work-group for the loss
+    hipLaunchKernelGGL(k_mlp_reduce, dim3((MLP_NP + RED_BLOCK - 1) / RED_BLOCK + 1), dim3(RED_BLOCK), 0, st, a);
     return hipGetLastError();
 }
 

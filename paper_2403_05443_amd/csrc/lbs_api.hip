@@ -142,7 +142,6 @@ lb_status lbs_train(lbs* s, const float* X, const float* Y, int n, int epochs, i
     lb_status st = upload(s, X, Y, n);
     if (st != LB_OK) return st;
     for (int e = 0; e < epochs; ++e) {
-        HC(hipMemsetAsync(s->loss_acc, 0, sizeof(double), s->stream));
         for (int b0 = 0; b0 < n; b0 += batch) {
             const int nb = std::min(batch, n - b0);
             MlpArgs a{s->P, s->X + (size_t)b0 * MLP_IN, s->Y + (size_t)b0 * MLP_OUT, nullptr, s->G, s->Lpart, nb,
@@ -160,6 +159,7 @@ lb_status lbs_train(lbs* s, const float* X, const float* Y, int n, int epochs, i
             r.c1 = (float)(1.0 / (1.0 - std::pow(0.9, (double)s->adam_t)));
             r.c2 = (float)(1.0 / (1.0 - std::pow(0.999, (double)s->adam_t)));
             r.loss_acc = s->loss_acc;
+            r.loss_first = b0 == 0;
             r.mode = 0;
             HC(launch_mlp_reduce(r, s->stream));
         }
@@ -186,7 +186,6 @@ lb_status lbs_grad(lbs* s, const float* X, const float* Y, int n, float* grads, 
     if (!s || !X || !Y || n < 1 || n > s->max_n) return LB_EINVAL;
     lb_status st = upload(s, X, Y, n);
     if (st != LB_OK) return st;
-    HC(hipMemsetAsync(s->loss_acc, 0, sizeof(double), s->stream));
     MlpArgs a{s->P, s->X, s->Y, nullptr, s->G, s->Lpart, n, (float)(2.0 / (6.0 * n)), 1};
     HC(launch_mlp(a, s->stream));
     MlpReduceArgs r{};
@@ -195,6 +194,7 @@ lb_status lbs_grad(lbs* s, const float* X, const float* Y, int n, float* grads, 
     r.ntiles = (n + 15) / 16;
     r.gsum = s->gsum;
     r.loss_acc = s->loss_acc;
+    r.loss_first = 1;
     r.mode = 1;
     HC(launch_mlp_reduce(r, s->stream));
     double acc = 0;

@@ -34,6 +34,7 @@
 // rigidly with its U, Omega.  Every node gets the second-order equilibrium
 // at its density and velocity, written as pre-collision populations (slot
 // (x - c_i, i)).
+#include <algorithm>
 #include <type_traits>
 
 #include "lbell_dev.h"
@@ -152,11 +153,11 @@ __global__ void k_warm_targets(const PartDev* __restrict__ parts, int np, const 
 }
 
 // minimum-image offset of node (x, y, z) from the particle centre
-__device__ __forceinline__ void offset(const PartDev& P, const BoxDesc& B, int x, int y, int z, double d[3]) {
+__device__ __forceinline__ void offset(const double xc[3], const BoxDesc& B, int x, int y, int z, double d[3]) {
     const int n[3] = {B.nx, B.ny, B.nz};
     const int c[3] = {x, y, z};
     for (int k = 0; k < 3; ++k) {
-        double v = c[k] - P.xc[k];
+        double v = c[k] - xc[k];
         if (v >= 0.5 * n[k]) v -= n[k];
         if (v < -0.5 * n[k]) v += n[k];
         d[k] = v;
@@ -168,23 +169,33 @@ constexpr int WM = (2 * WK + 1) * (2 * WK + 1) * (2 * WK + 1);  // mode slots pe
 
 __device__ __forceinline__ int wk_axis(int L) { return min(WK, (L - 1) / 2); }
 
-// Gauss-Legendre rules on [-1, 1] of 24, 16 and 12 points, one table: the
-// positive nodes and their weights of each (the rules are symmetric), at
-// rows 0, 12 and 20.
-__constant__ double GLTAB[26][2] = {
-    {0.06405689286260563, 0.12793819534675221}, {0.1911188674736163, 0.1258374563468283},
-    {0.3150426796961634, 0.12167047292780342},  {0.4337935076260451, 0.11550566805372561},
-    {0.5454214713888396, 0.1074442701159656},   {0.6480936519369755, 0.09761865210411406},
-    {0.7401241915785544, 0.08619016153195329},  {0.820001985973903, 0.07334648141108041},
-    {0.886415527004401, 0.05929858491543674},   {0.9382745520027328, 0.04427743881741955},
-    {0.9747285559713095, 0.028531388628933743}, {0.9951872199970213, 0.012341229799987091},
-    {0.09501250983763745, 0.18945061045506859}, {0.2816035507792589, 0.1826034150449236},
-    {0.45801677765722737, 0.16915651939500262}, {0.6178762444026438, 0.14959598881657676},
-    {0.755404408355003, 0.12462897125553403},   {0.8656312023878318, 0.09515851168249259},
-    {0.9445750230732326, 0.062253523938647706}, {0.9894009349916499, 0.027152459411754037},
-    {0.1252334085114689, 0.2491470458134027},   {0.3678314989981802, 0.23349253653835464},
-    {0.5873179542866175, 0.20316742672306565},  {0.7699026741943047, 0.1600783285433461},
-    {0.9041172563704748, 0.10693932599531888},  {0.9815606342467192, 0.04717533638651202},
+// Gauss-Legendre rules on [-1, 1] of 32, 24, 16, 12 and 8 points, one table:
+// the positive nodes and their weights of each (the rules are symmetric).
+constexpr int GL32 = 0, GL24 = 16, GL16 = 28, GL12 = 36, GL8 = 42;
+__constant__ double GLTAB[46][2] = {
+    {0.04830766568773832, 0.0965400885147278}, {0.1444719615827965, 0.09563872007927486},
+    {0.23928736225213706, 0.09384439908080457}, {0.33186860228212767, 0.09117387869576389},
+    {0.42135127613063533, 0.08765209300440381}, {0.5068999089322294, 0.08331192422694675},
+    {0.5877157572407623, 0.07819389578707031}, {0.6630442669302152, 0.0723457941088485},
+    {0.7321821187402897, 0.06582222277636185}, {0.7944837959679424, 0.058684093478535544},
+    {0.84936761373257, 0.050998059262376175}, {0.8963211557660521, 0.04283589802222668},
+    {0.9349060759377397, 0.03427386291302143}, {0.9647622555875064, 0.02539206530926206},
+    {0.9856115115452684, 0.01627439473090567}, {0.9972638618494816, 0.007018610009470096},
+    {0.06405689286260563, 0.12793819534675216}, {0.1911188674736163, 0.1258374563468283},
+    {0.3150426796961634, 0.12167047292780339}, {0.4337935076260451, 0.1155056680537256},
+    {0.5454214713888396, 0.10744427011596563}, {0.6480936519369755, 0.09761865210411388},
+    {0.7401241915785544, 0.08619016153195327}, {0.820001985973903, 0.0733464814110803},
+    {0.8864155270044011, 0.05929858491543678}, {0.9382745520027328, 0.04427743881741981},
+    {0.9747285559713095, 0.028531388628933663}, {0.9951872199970213, 0.0123412297999872},
+    {0.09501250983763744, 0.1894506104550685}, {0.2816035507792589, 0.18260341504492358},
+    {0.45801677765722737, 0.16915651939500254}, {0.6178762444026438, 0.14959598881657674},
+    {0.755404408355003, 0.12462897125553388}, {0.8656312023878318, 0.09515851168249279},
+    {0.9445750230732326, 0.062253523938647894}, {0.9894009349916499, 0.027152459411754096},
+    {0.1252334085114689, 0.24914704581340277}, {0.3678314989981802, 0.2334925365383548},
+    {0.5873179542866175, 0.20316742672306592}, {0.7699026741943047, 0.16007832854334622},
+    {0.9041172563704749, 0.10693932599531843}, {0.9815606342467192, 0.04717533638651183},
+    {0.1834346424956498, 0.362683783378362}, {0.525532409916329, 0.31370664587788727},
+    {0.7966664774136267, 0.22238103445337448}, {0.9602898564975362, 0.10122853629037626},
 };
 
 // Below this eccentricity a prolate spheroid's flow is taken as the sphere's
@@ -192,6 +203,8 @@ __constant__ double GLTAB[26][2] = {
 constexpr double E_LINE = 1e-4;
 constexpr int UF = 4;  // doubles per node of the staged free field: velocity, pressure
 constexpr int MC = 8;  // doubles per mode: (re, im) of velocity and pressure
+constexpr int MODE_HALF = (2 * WK + 1) * (WK + 1) * UF;   // (n_x, n_y >= 0, component) of a slab's sums
+constexpr int SLAB = MODE_HALF * (2 * WK + 1) * 2;         // doubles per slab: for each n_z, (re, im)
 constexpr int NPART = 8;  // partial sums per tile of k_stokes_sum
 
 __device__ __forceinline__ bool loaded(const PartDev& P) {
@@ -221,35 +234,51 @@ __device__ __forceinline__ bool loaded(const PartDev& P) {
 // e^2 / D1, alpha_c = 2 e^2 / D2; Omega = t_p D3 / (1 - e^2) + t_c D1 /
 // (2 - e^2); D1 = -2e + (1 + e^2) L, D2 = 2e + (3e^2 - 1) L, D3 = 2e -
 // (1 - e^2) L, L = ln((1 + e) / (1 - e)) (power series below e = 1/2, where
-// they cancel).  The segment integrals are taken with the substitution
-// xi = xi0 -+ delta sinh(t) about the point xi0 of the segment nearest d
-// (delta the distance to it), which smooths the near-tip peaks, and
-// Gauss-Legendre points on each side of xi0: 24 within delta < f / 2, 16
-// within delta < 3 f / 2, 12 beyond (each within ~2e-15 of the integral,
-// relative to the velocity, measured against adaptive quadrature).
+// they cancel).
+//
+// With d = z p + n, n across the axis, and zeta = z - xi, r = zeta p + n, so
+// (s.r) = s.n + zeta s.p, (r.m) = n.m (m is across p), and the flow is
+//   s A + n B + p (B_zeta + E) + (t x n) C + (t x p) C_zeta + m D
+// of eight scalar integrals over the segment (the eighth is the pressure).
+// The points of the integrals depend on delta, the distance from d to
+// the segment.  From 0.8 f on the integrands are smooth and plain
+// Gauss-Legendre over the whole segment converges: 32 points, 24 from
+// 1.15 f, 16 from 1.95 f, 12 from 3.2 f, 8 from 9 f (truncation below 1e-16 of
+// the velocity at these lines for aspect ratios 1.02 to 5, measured in
+// extended precision).  Nearer, the substitution xi = x0 -+ delta sinh(t) about
+// the point x0 of the segment nearest d smooths the peak, with
+// 24 points on each side of x0 within f / 2 and 16 beyond (within ~2e-15 of
+// the integral); the nodes +-x of a rule share one exponential,
+// e^t = e^(tm/2) e^(+-tm x/2).
 // Every other shape: the sphere of radius Req = (abc)^(1/3) moving with
 // F / (6 pi mu Req) and turning with T / (8 pi mu Req^3) (Stokes' solution
 // and the rotlet), rigid inside Req.
-__device__ void particle_flow(const PartDev& P, double mu, const double d[3], double u[4]) {
+//
+// FlowConst: everything above that does not depend on the node, once per
+// particle (k_stokes_prep).
+struct FlowConst {
+    double xc[3], p[3], S[3], Sp, G[3], Gp[3], m[3], U[3], W[3];
+    double f, if_, bfac, dl, ka, ia2, ib2, mu2, R;
+    int line, torque;
+};
+constexpr int FLOW_DOUBLES = (int)(sizeof(FlowConst) / sizeof(double));
+static_assert(sizeof(FlowConst) % sizeof(double) == 0, "FlowConst is stored in a scratch of doubles");
+
+__device__ void flow_const(const PartDev& P, double mu, FlowConst& C) {
     const double a = P.axes[0], b = P.axes[1];
     const double e2 = a > b && b == P.axes[2] ? 1.0 - (b / a) * (b / a) : 0.0;
-    if (e2 < E_LINE * E_LINE) {
-        const double r = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-        const double R = eq_radius(P);
+    for (int k = 0; k < 3; ++k) C.xc[k] = P.xc[k];
+    C.line = e2 >= E_LINE * E_LINE;
+    C.torque = P.Text[0] != 0.0 || P.Text[1] != 0.0 || P.Text[2] != 0.0;
+    C.mu2 = 2.0 * mu;
+    C.R = eq_radius(P);
+    if (!C.line) {
+        const double R = C.R;
         const double cu = 1.0 / (6.0 * M_PI * mu * R), cw = 1.0 / (8.0 * M_PI * mu * R * R * R);
-        const double U[3] = {P.Fext[0] * cu, P.Fext[1] * cu, P.Fext[2] * cu};
-        const double W[3] = {P.Text[0] * cw, P.Text[1] * cw, P.Text[2] * cw};
-        const double wx[3] = {W[1] * d[2] - W[2] * d[1], W[2] * d[0] - W[0] * d[2], W[0] * d[1] - W[1] * d[0]};
-        if (r < R) {
-            for (int k = 0; k < 3; ++k) u[k] += U[k] + wx[k];
-            return;
+        for (int k = 0; k < 3; ++k) {
+            C.U[k] = P.Fext[k] * cu;
+            C.W[k] = P.Text[k] * cw;
         }
-        const double ex[3] = {d[0] / r, d[1] / r, d[2] / r};
-        const double Ue = U[0] * ex[0] + U[1] * ex[1] + U[2] * ex[2];
-        const double a1 = 0.75 * R / r, a3 = 0.25 * R * R * R / (r * r * r), rr = (R / r) * (R / r) * (R / r);
-        for (int k = 0; k < 3; ++k)
-            u[k] += a1 * (U[k] + Ue * ex[k]) + a3 * (U[k] - 3.0 * Ue * ex[k]) + rr * wx[k];
-        u[3] += 1.5 * mu * R * Ue / (r * r);
         return;
     }
     const double e = sqrt(e2), f = a * e;
@@ -269,76 +298,171 @@ __device__ void particle_flow(const PartDev& P, double mu, const double d[3], do
         D2 = 2.0 * e + (3.0 * e2 - 1.0) * L;
         D3 = 2.0 * e - (1.0 - e2) * L;
     }
-    const double bfac = -(1.0 - e2) / (2.0 * e2), dl = 3.0 * e2 / (2.0 - e2), ka = (1.0 - e2) / (4.0 * (2.0 - e2));
+    C.f = f;
+    C.if_ = 1.0 / f;
+    C.bfac = -(1.0 - e2) / (2.0 * e2);
+    C.dl = 3.0 * e2 / (2.0 - e2);
+    C.ka = (1.0 - e2) / (4.0 * (2.0 - e2));
+    C.ia2 = 1.0 / (a * a);
+    C.ib2 = 1.0 / (b * b);
     double Rm[3][3];
     body_to_lab(P.q, Rm);
     const double p[3] = {Rm[0][0], Rm[1][0], Rm[2][0]};
     const double Fp = P.Fext[0] * p[0] + P.Fext[1] * p[1] + P.Fext[2] * p[2];
     const double Tp = P.Text[0] * p[0] + P.Text[1] * p[1] + P.Text[2] * p[2];
     const double cf = 1.0 / (16.0 * M_PI * mu * f), ct = 1.0 / (8.0 * M_PI * mu * (4.0 / 3.0) * f * f * f);
-    double U[3], W[3], S1[3], G[3], Gc[3];
+    double Gc[3];
     for (int k = 0; k < 3; ++k) {
-        S1[k] = P.Fext[k] * cf;
-        G[k] = P.Text[k] * ct;
+        C.p[k] = p[k];
+        C.S[k] = P.Fext[k] * cf;
+        C.G[k] = P.Text[k] * ct;
         Gc[k] = (P.Text[k] - Tp * p[k]) * ct;
-        U[k] = Fp * p[k] * cf * D1 / e2 + (P.Fext[k] - Fp * p[k]) * cf * D2 / (2.0 * e2);
-        W[k] = Tp * p[k] * ct * D3 / (1.0 - e2) + Gc[k] * D1 / (2.0 - e2);
+        C.U[k] = Fp * p[k] * cf * D1 / e2 + (P.Fext[k] - Fp * p[k]) * cf * D2 / (2.0 * e2);
+        C.W[k] = Tp * p[k] * ct * D3 / (1.0 - e2) + Gc[k] * D1 / (2.0 - e2);
     }
+    C.Sp = Fp * cf;
+    const double* G = C.G;
     const double m[3] = {Gc[1] * p[2] - Gc[2] * p[1], Gc[2] * p[0] - Gc[0] * p[2], Gc[0] * p[1] - Gc[1] * p[0]};
+    const double Gp[3] = {G[1] * p[2] - G[2] * p[1], G[2] * p[0] - G[0] * p[2], G[0] * p[1] - G[1] * p[0]};
+    for (int k = 0; k < 3; ++k) {
+        C.m[k] = m[k];
+        C.Gp[k] = Gp[k];
+    }
+}
+
+// One thread per particle: its constants, and the box it loads (-1: none).
+__global__ void k_stokes_prep(const PartDev* __restrict__ parts, int np, double mu, FlowConst* __restrict__ fc,
+                              int* __restrict__ pbox) {
+    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= np) return;
+    const bool use = loaded(parts[p]);
+    pbox[p] = use ? parts[p].box : -1;
+    if (use) flow_const(parts[p], mu, fc[p]);
+}
+
+// The eight integrals of particle_flow, a point at a time.
+struct LineSums {
+    double A, B, Bz, C, Cz, D, E, pr;
+};
+template <bool TORQUE>
+__device__ __forceinline__ void line_point(const FlowConst& K, double n2, double Sn, double nm, double zeta, double g,
+                                           double wq, LineSums& I) {
+    const double R2 = n2 + zeta * zeta;
+    const double iR = rsqrt(R2), iR2 = iR * iR, iR3 = iR * iR2;
+    const double Sr = Sn + K.Sp * zeta, cS3 = K.bfac * g * iR2;  // cS3 / R: the dipoles' weight over R^3
+    double B = Sr * iR3 * (1.0 + 3.0 * cS3), pr = Sr * iR3;
+    I.A += wq * (iR * (1.0 - cS3));
+    if constexpr (TORQUE) {
+        const double iR5 = iR3 * iR2, cQ = K.ka * g * g, rpm = zeta * nm * iR5, st = K.dl * g * rpm;
+        B += st - 15.0 * cQ * iR2 * rpm;
+        pr += st;
+        const double c = wq * g * iR3, q = 3.0 * wq * cQ * iR5;
+        I.C += c;
+        I.Cz += c * zeta;
+        I.D += q * zeta;
+        I.E += q * nm;
+    }
+    I.B += wq * B;
+    I.Bz += wq * B * zeta;
+    I.pr += wq * pr;
+}
+
+template <bool TORQUE>
+__device__ __forceinline__ void line_sums(const FlowConst& K, double z, double n2, double Sn, double nm, LineSums& I) {
+    const double f = K.f;
+    const double x0 = fmin(fmax(z, -f), f), zx = z - x0;
+    const double delta = sqrt(n2 + zx * zx);  // > 0: the segment lies inside the body
+    const double q = delta * K.if_;
+    // the rule is the wave's: the one its nearest node on this side of 0.8 f
+    // needs (so the table is read with scalar loads and no lane waits for a
+    // longer rule than its own row of nodes)
+    if (q >= 0.8) {
+        const bool b1 = __any(q < 1.15), b2 = __any(q < 1.95), b3 = __any(q < 3.2), b4 = __any(q < 9.0);
+        const int row = b1 ? GL32 : (b2 ? GL24 : (b3 ? GL16 : (b4 ? GL12 : GL8)));
+        const int half = b1 ? 16 : (b2 ? 12 : (b3 ? 8 : (b4 ? 6 : 4)));
+#pragma unroll 2
+        for (int j = 0; j < half; ++j) {
+            const double xi = f * GLTAB[row + j][0], wq = f * GLTAB[row + j][1], g = (f - xi) * (f + xi);
+            line_point<TORQUE>(K, n2, Sn, nm, z - xi, g, wq, I);
+            line_point<TORQUE>(K, n2, Sn, nm, z + xi, g, wq, I);
+        }
+        return;
+    }
+    const bool near = __any(q < 0.5);
+    const int row = near ? GL24 : GL16, half = near ? 12 : 8;
+    const double idel = 1.0 / delta;
+    for (int side = 0; side < 2; ++side) {
+        const double sgn = side ? 1.0 : -1.0, len = side ? f - x0 : x0 + f;
+        if (len <= 0.0) continue;
+        const double sl = len * idel, tm = asinh(sl), et = sqrt(sl + sqrt(1.0 + sl * sl)), it = 1.0 / et;
+        const double wh = 0.25 * tm * delta, hd = 0.5 * delta;
+        for (int j = 0; j < half; ++j) {
+            const double eh = exp(0.5 * tm * GLTAB[row + j][0]), ih = 1.0 / eh, w = wh * GLTAB[row + j][1];
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {  // e^t and e^-t of the two nodes
+                const double ep = v ? et * eh : et * ih, em = v ? it * ih : it * eh;
+                const double off = sgn * hd * (ep - em);  // xi = x0 + off
+                line_point<TORQUE>(K, n2, Sn, nm, zx - off, ((f - x0) - off) * ((f + x0) + off), w * (ep + em), I);
+            }
+        }
+    }
+}
+
+__device__ __forceinline__ void particle_flow(const FlowConst& K, const double d[3], double u[4]) {
+    const double *U = K.U, *W = K.W;
+    if (!K.line) {
+        const double r = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
+        const double R = K.R, mu = 0.5 * K.mu2;
+        const double wx[3] = {W[1] * d[2] - W[2] * d[1], W[2] * d[0] - W[0] * d[2], W[0] * d[1] - W[1] * d[0]};
+        if (r < R) {
+            for (int k = 0; k < 3; ++k) u[k] += U[k] + wx[k];
+            return;
+        }
+        const double ex[3] = {d[0] / r, d[1] / r, d[2] / r};
+        const double Ue = U[0] * ex[0] + U[1] * ex[1] + U[2] * ex[2];
+        const double a1 = 0.75 * R / r, a3 = 0.25 * R * R * R / (r * r * r), rr = (R / r) * (R / r) * (R / r);
+        for (int k = 0; k < 3; ++k)
+            u[k] += a1 * (U[k] + Ue * ex[k]) + a3 * (U[k] - 3.0 * Ue * ex[k]) + rr * wx[k];
+        u[3] += 1.5 * mu * R * Ue / (r * r);
+        return;
+    }
+    const double* p = K.p;
     const double z = d[0] * p[0] + d[1] * p[1] + d[2] * p[2];
-    const double rho2 = fmax(d[0] * d[0] + d[1] * d[1] + d[2] * d[2] - z * z, 0.0);
-    if (z * z / (a * a) + rho2 / (b * b) < 1.0) {  // inside: rigid motion
+    const double n[3] = {d[0] - z * p[0], d[1] - z * p[1], d[2] - z * p[2]};
+    const double n2 = n[0] * n[0] + n[1] * n[1] + n[2] * n[2];
+    if (z * z * K.ia2 + n2 * K.ib2 < 1.0) {  // inside: rigid motion
         u[0] += U[0] + W[1] * d[2] - W[2] * d[1];
         u[1] += U[1] + W[2] * d[0] - W[0] * d[2];
         u[2] += U[2] + W[0] * d[1] - W[1] * d[0];
         return;
     }
-    const double x0 = fmin(fmax(z, -f), f);
-    const double delta = sqrt(rho2 + (z - x0) * (z - x0));  // > 0: the segment lies inside the body
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    const int ng = delta < 0.5 * f ? 24 : delta < 1.5 * f ? 16 : 12, half = ng / 2;
-    const int row = ng == 24 ? 0 : ng == 16 ? 12 : 20;
-    for (int side = 0; side < 2; ++side) {
-        const double sgn = side ? 1.0 : -1.0, len = side ? f - x0 : x0 + f;
-        if (len <= 0.0) continue;
-        const double tm = asinh(len / delta);
-        for (int j = 0; j < ng; ++j) {
-            const int ri = row + (j < half ? half - 1 - j : j - half);
-            const double tj = j < half ? -GLTAB[ri][0] : GLTAB[ri][0], wj = GLTAB[ri][1];
-            const double t = 0.5 * tm * (tj + 1.0), et = exp(t), it = 1.0 / et;
-            const double xi = x0 + sgn * delta * 0.5 * (et - it);
-            const double wq = 0.5 * tm * wj * delta * 0.5 * (et + it);
-            const double r[3] = {d[0] - xi * p[0], d[1] - xi * p[1], d[2] - xi * p[2]};
-            const double R2 = r[0] * r[0] + r[1] * r[1] + r[2] * r[2];
-            const double iR = rsqrt(R2), iR2 = iR * iR, iR3 = iR * iR2, iR5 = iR3 * iR2, iR7 = iR5 * iR2;
-            const double g = (f - xi) * (f + xi);
-            const double Sr = S1[0] * r[0] + S1[1] * r[1] + S1[2] * r[2];
-            const double rp = r[0] * p[0] + r[1] * p[1] + r[2] * p[2];
-            const double rm = r[0] * m[0] + r[1] * m[1] + r[2] * m[2];
-            const double Gxr[3] = {G[1] * r[2] - G[2] * r[1], G[2] * r[0] - G[0] * r[2], G[0] * r[1] - G[1] * r[0]};
-            const double cS = bfac * g, cQ = ka * g * g;
-            for (int k = 0; k < 3; ++k) {
-                const double v = S1[k] * iR + Sr * r[k] * iR3                      // Stokeslets
-                                 + cS * (-S1[k] * iR3 + 3.0 * Sr * r[k] * iR5)     // potential dipoles
-                                 + g * Gxr[k] * iR3                                // rotlets
-                                 + dl * g * r[k] * rp * rm * iR5                   // stresslets
-                                 + cQ * (3.0 * (m[k] * rp + rm * p[k]) * iR5 - 15.0 * rm * rp * r[k] * iR7);
-                acc[k] += wq * v;
-            }
-            acc[3] += wq * 2.0 * mu * (Sr * iR3 + dl * g * rp * rm * iR5);
-        }
+    const double *S = K.S, *G = K.G;
+    const double Sn = S[0] * n[0] + S[1] * n[1] + S[2] * n[2];
+    LineSums I = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (K.torque) {  // the same for every node of the particle
+        line_sums<true>(K, z, n2, Sn, n[0] * K.m[0] + n[1] * K.m[1] + n[2] * K.m[2], I);
+        const double Gn[3] = {G[1] * n[2] - G[2] * n[1], G[2] * n[0] - G[0] * n[2], G[0] * n[1] - G[1] * n[0]};
+        for (int k = 0; k < 3; ++k) u[k] += Gn[k] * I.C + K.Gp[k] * I.Cz + K.m[k] * I.D;
+    } else {
+        line_sums<false>(K, z, n2, Sn, 0.0, I);
     }
-    for (int k = 0; k < 4; ++k) u[k] += acc[k];
+    for (int k = 0; k < 3; ++k) u[k] += S[k] * I.A + n[k] * I.B + p[k] * (I.Bz + I.E);
+    u[3] += K.mu2 * I.pr;
 }
 
 // Free-space flow and pressure of every node of the started boxes (the sum
 // over each box's loaded particles of particle_flow), node-major into uf at
 // UF * (ooff + site - base).  A work-group per tile; the box's loaded particles
 // are listed in index order, TILE at a time, in LDS.
-__global__ __launch_bounds__(TILE) void k_stokes_free(const BoxDesc* __restrict__ boxes,
+// Bound by FP64 arithmetic; four waves to a SIMD at the price of 30 spilled
+// values beat two without (440 against 565 us on 64 boxes, 7.7 M nodes;
+// 1507 us with the constants per node, two-sided rules everywhere and the
+// vector terms inside the quadrature).
+__global__ __launch_bounds__(TILE, 4) void k_stokes_free(const BoxDesc* __restrict__ boxes,
                                                       const int* __restrict__ tile_box,
-                                                      const PartDev* __restrict__ parts, int np, double mu,
-                                                      int only_box, long long base, double* __restrict__ uf) {
+                                                      const FlowConst* __restrict__ fc,
+                                                      const int* __restrict__ pbox, int np, int only_box,
+                                                      long long base, double* __restrict__ uf) {
     __shared__ int list[TILE];
     __shared__ int wcnt[TILE / 64];
     const int tile = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -350,7 +474,7 @@ __global__ __launch_bounds__(TILE) void k_stokes_free(const BoxDesc* __restrict_
     double u[UF] = {0.0, 0.0, 0.0, 0.0};
     for (int p0 = 0; p0 < np; p0 += TILE) {
         const int p = p0 + tid;
-        const bool take = p < np && parts[p].box == bi && loaded(parts[p]);
+        const bool take = p < np && pbox[p] == bi;
         const unsigned long long bal = __ballot(take);
         if (lane == 0) wcnt[wv] = __popcll(bal);
         __syncthreads();
@@ -363,21 +487,21 @@ __global__ __launch_bounds__(TILE) void k_stokes_free(const BoxDesc* __restrict_
         __syncthreads();
         if (s < B.n)
             for (int j = 0; j < cnt; ++j) {
-                const PartDev& P = parts[list[j]];
+                // one particle for the whole wave: its constants are scalar loads
+                const FlowConst& K = fc[__builtin_amdgcn_readfirstlane(list[j])];
                 double d[3];
-                offset(P, B, x, y, z, d);
-                particle_flow(P, mu, d, u);
+                offset(K.xc, B, x, y, z, d);
+                particle_flow(K, d, u);
             }
         __syncthreads();
     }
     if (s < B.n) {
-        double* o = uf + UF * (B.ooff + s - base);
-        for (int k = 0; k < UF; ++k) o[k] = u[k];
+        double2* o = reinterpret_cast<double2*>(uf + UF * (B.ooff + s - base));
+        o[0] = double2{u[0], u[1]};
+        o[1] = double2{u[2], u[3]};
     }
 }
 
-// Periodic correction Re sum_m c_m exp(i k_m . x) at node (x, y, z); c: the
-// box's WM x 3 complex coefficients (re, im), zero for unused slots.
 // exp(i 2 pi n x / L) for n = -WK..WK (WK = 2) into e[n + WK] (re, im):
 // powers of the n = 1 term, the negative ones conjugate.
 static_assert(WK == 2, "twiddles() builds the modes |n| <= 2");
@@ -402,71 +526,58 @@ __device__ __forceinline__ void twiddles(int x, int L, double e[2 * WK + 1][2]) 
 }
 
 // The periodic correction Re sum_m c_m exp(i k_m . x) at the nodes of one
-// tile, in two stages.  row_coefs (every thread of the work-group calls it):
-// for each row (y, z) the tile touches, R[a][k] = sum over (ny, nz) of
-// c_(a, ny, nz)[k] exp(i (ky y + kz z)) into LDS (slots outside the box's
-// mode set hold c = 0); then a node's correction is Re sum_a R[a][k]
-// exp(i kx x) (start_velocity).  c: the box's WM x MC coefficients.
-constexpr int CROWS = TILE / 4 + 2;  // rows a tile can touch (edges are at least 4)
-struct RowCoefs {
-    double tw[CROWS][2][2 * WK + 1][2];  // exp(i 2 pi n y / ny), exp(i 2 pi n z / nz) of each row
-    double R[CROWS][2 * WK + 1][UF][2];
-    int row0;
-};
+// tile, an axis at a time (row_coefs, called by every thread of the
+// work-group): for each plane z the tile touches, Z[a][b][k] = sum over n_z of
+// c_(a, b, n_z)[k] exp(i kz z); for each of its rows (y, z), R[a][k] = sum over
+// n_y of Z[a][b][k] exp(i ky y); then a node's correction is
+// Re sum_a R[a][k] exp(i kx x).  The corrected field is real, so the
+// coefficients of -n are the conjugates of those of n: a = 0..WK only, the terms
+// a > 0 counted twice.  c: the box's WM x MC coefficients (slots outside the
+// box's mode set hold 0).  5 + 5 products for each of 12 row coefficients
+// (25 for each of 20 when both axes were summed at once over all a).
+// The work-group's LDS is sized for the launch's boxes (plane_doubles for each plane
+// and row_doubles for each row a tile can touch), so that it does not bound
+// how many work-groups a compute unit holds.
+constexpr int PLANE_DOUBLES = (WK + 1) * (2 * WK + 1) * UF * 2, ROW_DOUBLES = (WK + 1) * UF * 2;
+// planes and rows a tile of an nx x ny x nz box can touch
+inline int tile_rows(int nx) { return (TILE - 2) / nx + 2; }
+inline int tile_planes(int nx, int ny) { return (tile_rows(nx) - 2) / ny + 2; }
 
-__device__ void row_coefs(const BoxDesc& B, const double* __restrict__ c, int s0, RowCoefs& rc) {
+// Fills Z (planes of the tile) and R (its rows); returns the tile's first row.
+__device__ int row_coefs(const BoxDesc& B, const double* __restrict__ c, int s0, double* Z, double* R) {
     const int tid = threadIdx.x, nt = blockDim.x;
-    const int row0 = s0 / B.nx, nrows = (min(s0 + TILE, B.n) - 1) / B.nx - row0 + 1;
-    if (tid == 0) rc.row0 = row0;
-    for (int r = tid; r < nrows; r += nt) {
-        const int row = row0 + r;
-        twiddles(row % B.ny, B.ny, rc.tw[r][0]);
-        twiddles(row / B.ny, B.nz, rc.tw[r][1]);
-    }
-    __syncthreads();
-    for (int t = tid; t < nrows * (2 * WK + 1) * UF; t += nt) {
-        const int r = t / ((2 * WK + 1) * UF), a = (t / UF) % (2 * WK + 1), k = t % UF;
-        double re = 0.0, im = 0.0;
-        for (int iz = 0; iz < 2 * WK + 1; ++iz) {
-            const double cz = rc.tw[r][1][iz][0], sz = rc.tw[r][1][iz][1];
-            for (int iy = 0; iy < 2 * WK + 1; ++iy) {
-                const double cy = rc.tw[r][0][iy][0], sy = rc.tw[r][0][iy][1];
-                const double er = cy * cz - sy * sz, ei = sy * cz + cy * sz;  // exp(i (ky y + kz z))
-                const double* cm = c + MC * (a + (2 * WK + 1) * (iy + (2 * WK + 1) * iz));
-                re += cm[2 * k] * er - cm[2 * k + 1] * ei;
-                im += cm[2 * k] * ei + cm[2 * k + 1] * er;
-            }
+    const int row0 = s0 / B.nx, row1 = (min(s0 + TILE, B.n) - 1) / B.nx;
+    const int z0 = row0 / B.ny, nplanes = row1 / B.ny - z0 + 1, nrows = row1 - row0 + 1;
+    constexpr int NB = 2 * WK + 1, PER_Z = PLANE_DOUBLES / 2, PER_ROW = ROW_DOUBLES / 2;
+    for (int t = tid; t < nplanes * PER_Z; t += nt) {  // item (plane, a, b, k)
+        const int zi = t / PER_Z, a = (t / (NB * UF)) % (WK + 1), b = (t / UF) % NB, k = t % UF;
+        double e[NB][2], re = 0.0, im = 0.0;
+        twiddles(z0 + zi, B.nz, e);
+#pragma unroll
+        for (int iz = 0; iz < NB; ++iz) {
+            const double* cm = c + MC * ((WK + a) + NB * (b + NB * iz)) + 2 * k;
+            re += cm[0] * e[iz][0] - cm[1] * e[iz][1];
+            im += cm[0] * e[iz][1] + cm[1] * e[iz][0];
         }
-        rc.R[r][a][k][0] = re;
-        rc.R[r][a][k][1] = im;
+        Z[2 * t] = re;
+        Z[2 * t + 1] = im;
     }
     __syncthreads();
-}
-
-// Velocity and pressure of site s = (x, y, z) of box B before the mean
-// corrections: rigid motion and no pressure inside a particle, else the
-// corrected load-driven flow (uf: the free flow of k_stokes_free; rc: the
-// tile's row_coefs).
-__device__ void start_velocity(const BoxDesc& B, uint16_t owner, const PartDev* __restrict__ parts,
-                               const double* __restrict__ uf, long long base, const RowCoefs& rc, int s, int x,
-                               int y, int z, double u[UF]) {
-    if (owner != 0) {
-        const PartDev& P = parts[owner - 1];
-        double d[3];
-        offset(P, B, x, y, z, d);
-        u[0] = P.U[0] + P.W[1] * d[2] - P.W[2] * d[1];
-        u[1] = P.U[1] + P.W[2] * d[0] - P.W[0] * d[2];
-        u[2] = P.U[2] + P.W[0] * d[1] - P.W[1] * d[0];
-        u[3] = 0.0;
-        return;
+    for (int t = tid; t < nrows * PER_ROW; t += nt) {  // item (row, a, k)
+        const int r = t / PER_ROW, a = (t / UF) % (WK + 1), k = t % UF, row = row0 + r, zi = row / B.ny - z0;
+        double e[NB][2], re = 0.0, im = 0.0;
+        twiddles(row % B.ny, B.ny, e);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const double* zz = Z + 2 * (((zi * (WK + 1) + a) * NB + b) * UF + k);
+            re += zz[0] * e[b][0] - zz[1] * e[b][1];
+            im += zz[0] * e[b][1] + zz[1] * e[b][0];
+        }
+        R[2 * t] = a ? 2.0 * re : re;
+        R[2 * t + 1] = a ? 2.0 * im : im;
     }
-    const double* o = uf + UF * (B.ooff + s - base);
-    for (int k = 0; k < UF; ++k) u[k] = o[k];
-    double ex[2 * WK + 1][2];
-    twiddles(x, B.nx, ex);
-    const int r = s / B.nx - rc.row0;
-    for (int a = 0; a < 2 * WK + 1; ++a)
-        for (int k = 0; k < UF; ++k) u[k] += rc.R[r][a][k][0] * ex[a][0] - rc.R[r][a][k][1] * ex[a][1];
+    __syncthreads();
+    return row0;
 }
 
 __device__ __forceinline__ double wave_sum(double v) {
@@ -474,105 +585,165 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
-// Discrete Fourier sums S_m = sum_x (u, p)_free(x) exp(-i k_m . x) over every
-// node of a box, for the modes of one (ny, nz) pair and all nx: work-group
-// 25 b + g takes box b and pair g, so the 25 work-groups of a box run
-// together and stream its staged field through the caches about once.
-// Edges up to TW_MAX take their phase factors from tables in LDS.
-constexpr int TW_MAX = 1024;
+// Discrete Fourier sums S_n = sum_x (u, p)_free(x) exp(-i k_n . x), |n_i| <= WK,
+// over the planes z = slab, slab + nslab, ... of a box, an axis at a time (the
+// field is real, so n_y >= 0 suffices: the others are conjugates).  Along y:
+// a thread keeps one x and sums its rows of the plane for n_y = 0..WK (20 sums,
+// 20 multiply-adds per node; consecutive threads read consecutive nodes).
+// Along x: 60 outputs (n_x, n_y, component) from those sums in LDS, four threads to
+// an output.  Along z: the plane's outputs times exp(-i kz z) for the five n_z,
+// kept in registers over the slab's planes.  The field is read once, about 60
+// operations a node; a work-group per (n_y, n_z) pair read it 25 times over and
+// spent 400 a node in all.  One 96^3 box 1500 -> 25 us (25 -> 96 work-groups), 64
+// boxes of edges 32-64 (7.7 M nodes) 1108 -> 168 us.
+constexpr int YT = 128;  // rows of the phase table held in LDS at a time
 __global__ __launch_bounds__(256) void k_stokes_modes(const BoxDesc* __restrict__ boxes,
                                                       const double* __restrict__ uf, long long base, int only_box,
-                                                      double* __restrict__ S) {
-    __shared__ double red[4][2 * WK + 1][MC];
-    __shared__ double tw[3][TW_MAX][2];  // exp(i 2 pi x / nx), exp(i 2 pi ny' y / ny), exp(i 2 pi nz' z / nz)
-    const int g = blockIdx.x % ((2 * WK + 1) * (2 * WK + 1)), bi = blockIdx.x / ((2 * WK + 1) * (2 * WK + 1));
+                                                      int box_slabs, double* __restrict__ S) {
+    __shared__ double Bs[(2 * WK + 1) * UF][256];
+    __shared__ double ty[YT][4], tx[256][4];  // (cos, sin) of n = 1 and of n = 2
+    const int bi = blockIdx.x / box_slabs, slab = blockIdx.x % box_slabs, tid = threadIdx.x;
     if (only_box >= 0 && bi != only_box) return;  // uniform over the block
     const BoxDesc& B = boxes[bi];
-    const int ny_ = g % (2 * WK + 1) - WK, nz_ = g / (2 * WK + 1) - WK;
-    const int Kx = wk_axis(B.nx), Ky = wk_axis(B.ny), Kz = wk_axis(B.nz);
-    if (abs(ny_) > Ky || abs(nz_) > Kz) return;  // uniform over the block
-    const bool tab = B.nx <= TW_MAX && B.ny <= TW_MAX && B.nz <= TW_MAX;
-    if (tab) {
-        for (int i = threadIdx.x; i < B.nx; i += blockDim.x) sincospi(2.0 * i / B.nx, &tw[0][i][1], &tw[0][i][0]);
-        for (int i = threadIdx.x; i < B.ny; i += blockDim.x)
-            sincospi(2.0 * ny_ * i / B.ny, &tw[1][i][1], &tw[1][i][0]);
-        for (int i = threadIdx.x; i < B.nz; i += blockDim.x)
-            sincospi(2.0 * nz_ * i / B.nz, &tw[2][i][1], &tw[2][i][0]);
-    }
-    __syncthreads();
-    double acc[2 * WK + 1][MC];
+    if (slab >= B.nslab) return;  // uniform over the block
+    const int nx = B.nx, ny = B.ny, nz = B.nz;
+    auto phase = [](double (&t)[4], int i, int n) {
+        double c, s;
+        sincospi(2.0 * i / n, &s, &c);
+        t[0] = c;
+        t[1] = s;
+        t[2] = c * c - s * s;
+        t[3] = 2.0 * s * c;
+    };
+    const int o = tid % MODE_HALF, seg = tid / MODE_HALF;  // output and its share of the x sum
+    const int ok = o % UF, oy = (o / UF) % (WK + 1), ox = o / (UF * (WK + 1)) - WK;
+    constexpr int NSEG = 256 / MODE_HALF;
+    double Zr[2 * WK + 1], Zi[2 * WK + 1];
 #pragma unroll
-    for (int a = 0; a < 2 * WK + 1; ++a)
+    for (int k = 0; k < 2 * WK + 1; ++k) Zr[k] = Zi[k] = 0.0;
+    for (int z = slab; z < nz; z += B.nslab) {
+        double pr = 0.0, pi = 0.0;
+        for (int x0 = 0; x0 < nx; x0 += 256) {
+            const int cw = min(256, nx - x0), ng = 256 / cw, g = tid / cw, x = x0 + tid % cw;
+            if (tid < cw && (nx > 256 || z == slab)) phase(tx[tid], x0 + tid, nx);
+            double acc[UF][2 * WK + 1];
 #pragma unroll
-        for (int k = 0; k < MC; ++k) acc[a][k] = 0.0;
-    for (int s = threadIdx.x; s < B.n; s += blockDim.x) {
-        const int x = s % B.nx, t = s / B.nx, y = t % B.ny, z = t / B.ny;
-        const double* o = uf + UF * (B.ooff + s - base);
-        const double u[UF] = {o[0], o[1], o[2], o[3]};
-        double syz, cyz, ex[2 * WK + 1][2];
-        if (tab) {
-            cyz = tw[1][y][0] * tw[2][z][0] - tw[1][y][1] * tw[2][z][1];
-            syz = tw[1][y][1] * tw[2][z][0] + tw[1][y][0] * tw[2][z][1];
-            powers(tw[0][x][0], tw[0][x][1], ex);
-        } else {
-            sincospi(2.0 * ((double)ny_ * y / B.ny + (double)nz_ * z / B.nz), &syz, &cyz);
-            twiddles(x, B.nx, ex);
-        }
+            for (int k = 0; k < UF; ++k)
 #pragma unroll
-        for (int nx = -WK; nx <= WK; ++nx) {  // fixed trip count: the accumulators stay in registers
-            if (nx < -Kx || nx > Kx) continue;
-            const double cx_ = ex[nx + WK][0], sx = ex[nx + WK][1];
-            // exp(-i theta) = cos theta - i sin theta, theta = kx x + ky y + kz z
-            const double c = cx_ * cyz - sx * syz, sn = sx * cyz + cx_ * syz;
+                for (int j = 0; j < 2 * WK + 1; ++j) acc[k][j] = 0.0;
+            for (int y0 = 0; y0 < ny; y0 += YT) {
+                const int y1 = min(ny, y0 + YT);
+                if (ny > YT || (x0 == 0 && z == slab)) {
+                    __syncthreads();
+                    if (tid < y1 - y0) phase(ty[tid], y0 + tid, ny);
+                    __syncthreads();
+                }
+                if (g < ng) {
+                    const double* row = uf + UF * (B.ooff + x + (long long)nx * ny * z - base);
+#pragma unroll 8
+                    for (int y = y0 + g; y < y1; y += ng) {
+                        const double2* q = reinterpret_cast<const double2*>(row + (long long)UF * nx * y);
+                        const double2 q0 = q[0], q1 = q[1];
+                        const double u[UF] = {q0.x, q0.y, q1.x, q1.y};
+                        const double* e = ty[y - y0];
 #pragma unroll
-            for (int k = 0; k < UF; ++k) {
-                acc[nx + WK][2 * k] += u[k] * c;
-                acc[nx + WK][2 * k + 1] -= u[k] * sn;
+                        for (int k = 0; k < UF; ++k) {
+                            acc[k][0] += u[k];
+#pragma unroll
+                            for (int j = 0; j < WK; ++j) {
+                                acc[k][1 + 2 * j] += u[k] * e[2 * j];
+                                acc[k][2 + 2 * j] -= u[k] * e[2 * j + 1];
+                            }
+                        }
+                    }
+                }
             }
+#pragma unroll
+            for (int k = 0; k < UF; ++k)
+#pragma unroll
+                for (int j = 0; j < 2 * WK + 1; ++j) Bs[k * (2 * WK + 1) + j][tid] = acc[k][j];
+            __syncthreads();
+            if (ng > 1) {  // the thread groups' sums of each x, into the first group's place
+                for (int i = tid; i < (2 * WK + 1) * UF * cw; i += 256) {
+                    const int j = i / cw, xx = i % cw;
+                    double v = Bs[j][xx];
+                    for (int h = 1; h < ng; ++h) v += Bs[j][h * cw + xx];
+                    Bs[j][xx] = v;
+                }
+                __syncthreads();
+            }
+            if (seg < NSEG) {
+                const double* br = Bs[ok * (2 * WK + 1) + (oy ? 2 * oy - 1 : 0)];
+                const double* bm = Bs[ok * (2 * WK + 1) + (oy ? 2 * oy : 0)];
+                const int an = ox < 0 ? -ox : ox;
+                for (int xx = seg; xx < cw; xx += NSEG) {
+                    const double c = an ? tx[xx][2 * an - 2] : 1.0;
+                    const double sn = an ? (ox < 0 ? -tx[xx][2 * an - 1] : tx[xx][2 * an - 1]) : 0.0;
+                    const double r = br[xx], m = oy ? bm[xx] : 0.0;
+                    pr += r * c + m * sn;  // (r + i m) (c - i sn)
+                    pi += m * c - r * sn;
+                }
+            }
+            __syncthreads();
+        }
+        double e[2 * WK + 1][2];
+        twiddles(z, nz, e);
+#pragma unroll
+        for (int k = 0; k < 2 * WK + 1; ++k) {  // exp(-i kz z)
+            Zr[k] += pr * e[k][0] + pi * e[k][1];
+            Zi[k] += pi * e[k][0] - pr * e[k][1];
         }
     }
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    double* red = &Bs[0][0];  // NSEG x SLAB
+    if (seg < NSEG)
 #pragma unroll
-    for (int a = 0; a < 2 * WK + 1; ++a)
-#pragma unroll
-        for (int k = 0; k < MC; ++k) {
-            const double v = wave_sum(acc[a][k]);
-            if (lane == 0) red[wv][a][k] = v;
+        for (int k = 0; k < 2 * WK + 1; ++k) {
+            red[seg * SLAB + (o * (2 * WK + 1) + k) * 2] = Zr[k];
+            red[seg * SLAB + (o * (2 * WK + 1) + k) * 2 + 1] = Zi[k];
         }
     __syncthreads();
-    if (threadIdx.x < (2 * WK + 1) * MC) {
-        const int a = threadIdx.x / MC, k = threadIdx.x % MC;
-        const double v = red[0][a][k] + red[1][a][k] + red[2][a][k] + red[3][a][k];
-        const int m = a + (2 * WK + 1) * ((ny_ + WK) + (2 * WK + 1) * (nz_ + WK));
-        S[((long long)bi * WM + m) * MC + k] = v;
+    for (int i = tid; i < SLAB; i += 256) {
+        double v = red[i];
+        for (int h = 1; h < NSEG; ++h) v += red[h * SLAB + i];
+        S[(long long)(B.slab0 + slab) * SLAB + i] = v;
     }
 }
+static_assert((256 / MODE_HALF) * SLAB <= (2 * WK + 1) * UF * 256, "the slab's sums are reduced in the place of Bs");
 
-// Correction coefficients: one thread per (box, mode slot): the periodic
-// solution's coefficient of every particle of the box minus the free flow's
-// DFT coefficient S_m / N; zero for slots outside the box's mode set.  The
-// pressure's is -i (k.f) / k^2 of the force density f (the torque's has no
-// divergence and drives none).
-__global__ void k_stokes_coef(const BoxDesc* __restrict__ boxes, int nboxes, const PartDev* __restrict__ parts,
-                              int np, double mu, const double* __restrict__ S, double* __restrict__ C) {
-    const int id = blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= nboxes * WM) return;
-    const int bi = id / WM, m = id % WM;
+// Correction coefficients, a work-group per box and a thread per mode slot:
+// the periodic solution's coefficient of every loaded particle of the box
+// minus the free flow's DFT coefficient S_m / N (its slabs summed in order);
+// zero for slots outside the box's mode set.  The pressure's is -i (k.f) / k^2
+// of the force density f (the torque's has no divergence and drives none).
+__global__ __launch_bounds__(128) void k_stokes_coef(const BoxDesc* __restrict__ boxes,
+                                                     const PartDev* __restrict__ parts,
+                                                     const int* __restrict__ pbox, int np, double mu, int only_box,
+                                                     const double* __restrict__ S, double* __restrict__ C) {
+    __shared__ int list[128];
+    __shared__ int wcnt[2];
+    const int bi = blockIdx.x, m = threadIdx.x, lane = m & 63, wv = m >> 6;
+    if (only_box >= 0 && bi != only_box) return;  // uniform over the block
     const BoxDesc& B = boxes[bi];
     const int n[3] = {m % (2 * WK + 1) - WK, (m / (2 * WK + 1)) % (2 * WK + 1) - WK, m / ((2 * WK + 1) * (2 * WK + 1)) - WK};
     const int L[3] = {B.nx, B.ny, B.nz};
-    double* c = C + (long long)id * MC;
-    bool use = !(n[0] == 0 && n[1] == 0 && n[2] == 0);
+    bool use = m < WM && !(n[0] == 0 && n[1] == 0 && n[2] == 0);
     for (int a = 0; a < 3; ++a) use = use && abs(n[a]) <= wk_axis(L[a]);
-    for (int k = 0; k < MC; ++k) c[k] = 0.0;
-    if (!use) return;
+    double c[MC] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     const double V = (double)B.n;
     double k[3];
     for (int a = 0; a < 3; ++a) k[a] = 2.0 * M_PI * n[a] / L[a];
     const double k2 = k[0] * k[0] + k[1] * k[1] + k[2] * k[2];
-    for (int p = 0; p < np; ++p) {
-        const PartDev& P = parts[p];
-        if (P.box != bi) continue;
+    for (int p0 = 0; p0 < np; p0 += 128) {
+      const int pt = p0 + m;
+      const bool take = pt < np && pbox[pt] == bi;
+      const unsigned long long bal = __ballot(take);
+      if (lane == 0) wcnt[wv] = __popcll(bal);
+      __syncthreads();
+      if (take) list[(wv ? wcnt[0] : 0) + __popcll(bal & ((1ull << lane) - 1ull))] = pt;
+      __syncthreads();
+      const int cnt = use ? wcnt[0] + wcnt[1] : 0;
+      for (int j = 0; j < cnt; ++j) {
+        const PartDev& P = parts[list[j]];
         // The traction of a body in rigid motion is sigma(x) (F + C x), sigma
         // the unit sphere's uniform layer mapped onto the surface: for an
         // ellipsoid (diag(a, b, c) in the body frame) its transform is
@@ -622,35 +793,73 @@ __global__ void k_stokes_coef(const BoxDesc* __restrict__ boxes, int nboxes, con
         const double pre = -3.0 * kg * j1k / k2 / V, pim = -kF * sinc / k2 / V;
         c[6] += pre * cp - pim * sp;
         c[7] += pre * sp + pim * cp;
+      }
+      __syncthreads();
     }
-    for (int a = 0; a < UF; ++a) {
-        c[2 * a] -= S[(long long)id * MC + 2 * a] / V;
-        c[2 * a + 1] -= S[(long long)id * MC + 2 * a + 1] / V;
+    if (use) {
+        // the slab sums hold n_y >= 0; a slot below it is the conjugate of -n
+        const int sg = n[1] < 0 ? -1 : 1;
+        const int o = ((sg * n[0] + WK) * (WK + 1) + sg * n[1]) * UF, iz = sg * n[2] + WK;
+        double d[MC] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+        for (int h = 0; h < B.nslab; ++h) {
+            const double* q = S + (long long)(B.slab0 + h) * SLAB;
+#pragma unroll
+            for (int a = 0; a < UF; ++a) {
+                d[2 * a] += q[((o + a) * (2 * WK + 1) + iz) * 2];
+                d[2 * a + 1] += q[((o + a) * (2 * WK + 1) + iz) * 2 + 1];
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < UF; ++a) {
+            c[2 * a] -= d[2 * a] / V;
+            c[2 * a + 1] -= sg * d[2 * a + 1] / V;
+        }
     }
+    if (m < WM)
+        for (int a = 0; a < MC; ++a) C[((long long)bi * WM + m) * MC + a] = c[a];
 }
 
-// partial sums over the fluid nodes of each tile: sum of u (3), of p u (3),
-// of p and the count
+// The periodic correction added to the staged field at every fluid node, in
+// place, and the tile's partial sums over its fluid nodes: of u (3), of p u
+// (3), of p and the count.  Writing the corrected field back costs 32 bytes a
+// node and spares k_stokes_write the correction (64 boxes: 411 -> 192 us here,
+// 463 -> 207 us there).
 __global__ __launch_bounds__(TILE) void k_stokes_sum(const BoxDesc* __restrict__ boxes,
                                                      const int* __restrict__ tile_box,
                                                      const uint16_t* __restrict__ omap,
-                                                     const PartDev* __restrict__ parts,
-                                                     const double* __restrict__ uf, long long base, int only_box,
-                                                     const double* __restrict__ coef,
+                                                     double* __restrict__ uf, long long base, int only_box,
+                                                     const double* __restrict__ coef, int planes,
                                                      double* __restrict__ partial) {
-    __shared__ double red[NPART][TILE];
-    __shared__ RowCoefs rc;
+    extern __shared__ double zr[];  // planes x PLANE_DOUBLES, then the rows
+    __shared__ double red[TILE / 64][NPART];
+    double *Z = zr, *R = zr + planes * PLANE_DOUBLES;
     const int tile = blockIdx.x, tid = threadIdx.x;
     const int bi = tile_box[tile];
     const BoxDesc& B = boxes[bi];
     const int s = (tile - B.tile0) * TILE + tid;
     double v[NPART] = {0, 0, 0, 0, 0, 0, 0, 0};
     const bool started = only_box < 0 || bi == only_box;  // uniform over the block
-    if (started) row_coefs(B, coef + (long long)bi * WM * MC, (tile - B.tile0) * TILE, rc);
+    int row0 = 0;
+    if (started) row0 = row_coefs(B, coef + (long long)bi * WM * MC, (tile - B.tile0) * TILE, Z, R);
     if (started && s < B.n && omap[B.ooff + s] == 0) {
-        const int x = s % B.nx, t = s / B.nx, y = t % B.ny, z = t / B.ny;
-        double u[UF];
-        start_velocity(B, 0, parts, uf, base, rc, s, x, y, z, u);
+        double2* o = reinterpret_cast<double2*>(uf + UF * (B.ooff + s - base));
+        const double2 q0 = o[0], q1 = o[1];
+        double u[UF] = {q0.x, q0.y, q1.x, q1.y};
+        int x;
+        const int row = div_magic(s, B.nx, B.mnx, B.lnx, x);
+        const double* Rr = R + (row - row0) * ROW_DOUBLES;  // [a][k] (re, im)
+        double ex[2 * WK + 1][2];
+        twiddles(x, B.nx, ex);
+#pragma unroll
+        for (int k = 0; k < UF; ++k) {
+            u[k] += Rr[2 * k];
+#pragma unroll
+            for (int a = 1; a <= WK; ++a)
+                u[k] += Rr[2 * (a * UF + k)] * ex[WK + a][0] - Rr[2 * (a * UF + k) + 1] * ex[WK + a][1];
+        }
+        o[0] = double2{u[0], u[1]};
+        o[1] = double2{u[2], u[3]};
         for (int k = 0; k < 3; ++k) {
             v[k] = u[k];
             v[3 + k] = u[3] * u[k];
@@ -658,36 +867,46 @@ __global__ __launch_bounds__(TILE) void k_stokes_sum(const BoxDesc* __restrict__
         v[6] = u[3];
         v[7] = 1.0;
     }
-    for (int k = 0; k < NPART; ++k) red[k][tid] = v[k];
-    __syncthreads();
-    for (int h = TILE / 2; h > 0; h >>= 1) {
-        if (tid < h)
-            for (int k = 0; k < NPART; ++k) red[k][tid] += red[k][tid + h];
-        __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NPART; ++k) {
+        const double w = wave_sum(v[k]);
+        if ((tid & 63) == 0) red[tid >> 6][k] = w;
     }
-    if (tid < NPART) partial[(long long)tile * NPART + tid] = red[tid][0];
+    __syncthreads();
+    if (tid < NPART) {
+        double w = 0.0;
+        for (int h = 0; h < TILE / 64; ++h) w += red[h][tid];
+        partial[(long long)tile * NPART + tid] = w;
+    }
 }
 
-// One wave per box: the mean pressure pbar of its fluid nodes and the
+// A work-group per box: the mean pressure pbar of its fluid nodes and the
 // uniform velocity ubar removed from them.  A fluid node gets the density
 // rho = rho0 + 3 (p - pbar) (p = c_s^2 (rho - rho0)), so the fluid's mass is
 // unchanged, and ubar = (sum rho u + sum_p M U) / (N rho0) makes the box's
 // momentum sum rho (u - ubar) + sum_p M U zero.
-__global__ __launch_bounds__(64) void k_stokes_mean(const BoxDesc* __restrict__ boxes,
+__global__ __launch_bounds__(256) void k_stokes_mean(const BoxDesc* __restrict__ boxes,
                                                     const PartDev* __restrict__ parts, int np,
                                                     const double* __restrict__ partial, double rho0,
                                                     double* __restrict__ ubar) {
-    const int b = blockIdx.x, lane = threadIdx.x;  // one 64-wide work-group per box
+    __shared__ double red[4][NPART + 3];
+    const int b = blockIdx.x, tid = threadIdx.x;
     const BoxDesc& B = boxes[b];
     double S[NPART] = {0, 0, 0, 0, 0, 0, 0, 0}, MU[3] = {0, 0, 0};
-    for (int t = B.tile0 + lane; t < B.tile0 + B.ntiles; t += 64)
+    for (int t = B.tile0 + tid; t < B.tile0 + B.ntiles; t += 256)
         for (int k = 0; k < NPART; ++k) S[k] += partial[(long long)t * NPART + k];
-    for (int p = lane; p < np; p += 64)
+    for (int p = tid; p < np; p += 256)
         if (parts[p].box == b)
             for (int k = 0; k < 3; ++k) MU[k] += parts[p].M * parts[p].U[k];
-    for (int k = 0; k < NPART; ++k) S[k] = wave_sum(S[k]);
-    for (int k = 0; k < 3; ++k) MU[k] = wave_sum(MU[k]);
-    if (lane != 0) return;
+#pragma unroll
+    for (int k = 0; k < NPART + 3; ++k) {
+        const double v = wave_sum(k < NPART ? S[k] : MU[k - NPART]);
+        if ((tid & 63) == 0) red[tid >> 6][k] = v;
+    }
+    __syncthreads();
+    if (tid != 0) return;
+    for (int k = 0; k < NPART; ++k) S[k] = (red[0][k] + red[1][k]) + (red[2][k] + red[3][k]);
+    for (int k = 0; k < 3; ++k) MU[k] = (red[0][NPART + k] + red[1][NPART + k]) + (red[2][NPART + k] + red[3][NPART + k]);
     const double N = S[7], pbar = N > 0 ? S[6] / N : 0.0;
     double J[3];
     for (int k = 0; k < 3; ++k) J[k] = rho0 * S[k] + 3.0 * (S[3 + k] - pbar * S[k]) + MU[k];
@@ -695,47 +914,66 @@ __global__ __launch_bounds__(64) void k_stokes_mean(const BoxDesc* __restrict__ 
     ubar[4 * b + 3] = pbar;
 }
 
-template <int ST, int Q>
+// Bound by memory (a staged node read, Q populations written); the storage
+// convention is a template parameter so that a slot costs an addition, and the
+// two directions of a pair share their products.
+template <int ST, int Q, int CV>
 __global__ __launch_bounds__(TILE) void k_stokes_write(const BoxDesc* __restrict__ boxes,
                                                        const int* __restrict__ tile_box,
                                                        const uint16_t* __restrict__ omap,
                                                        const PartDev* __restrict__ parts,
                                                        const double* __restrict__ uf, long long base,
-                                                       const double* __restrict__ coef,
                                                        const double* __restrict__ ubar,
                                                        typename Store<ST>::T* __restrict__ f, KParams kp,
                                                        int only_box) {
     using S = Store<ST>;
-    __shared__ RowCoefs rc;
     const int tile = blockIdx.x;
     const int bi = tile_box[tile];
     if (only_box >= 0 && bi != only_box) return;  // uniform over the block
     const BoxDesc& B = boxes[bi];
-    row_coefs(B, coef + (long long)bi * WM * MC, (tile - B.tile0) * TILE, rc);
     const int s = (tile - B.tile0) * TILE + (int)threadIdx.x;
     if (s >= B.n) return;
     const uint16_t owner = omap[B.ooff + s];
     if (owner == 0xFFFF) return;
     const int nx = B.nx, ny = B.ny, nz = B.nz;
-    const int x = s % nx, t = s / nx, y = t % ny, z = t / ny;
-    double u[UF];
-    start_velocity(B, owner, parts, uf, base, rc, s, x, y, z, u);
+    int x, y;
+    const int z = div_magic(div_magic(s, nx, B.mnx, B.lnx, x), ny, B.mny, B.lny, y);
     const double rho0 = kp.rho0;
-    double rho = rho0;
+    double rho = rho0, u[3];
     if (owner == 0) {
-        for (int k = 0; k < 3; ++k) u[k] -= ubar[4 * bi + k];
-        rho = rho0 + 3.0 * (u[3] - ubar[4 * bi + 3]);
+        const double2* o = reinterpret_cast<const double2*>(uf + UF * (B.ooff + s - base));
+        const double2 q0 = o[0], q1 = o[1];
+        u[0] = q0.x - ubar[4 * bi];
+        u[1] = q0.y - ubar[4 * bi + 1];
+        u[2] = q1.x - ubar[4 * bi + 2];
+        rho = rho0 + 3.0 * (q1.y - ubar[4 * bi + 3]);
+    } else {  // rigid motion at the rest density inside a particle
+        const PartDev& P = parts[owner - 1];
+        double d[3];
+        offset(P.xc, B, x, y, z, d);
+        u[0] = P.U[0] + P.W[1] * d[2] - P.W[2] * d[1];
+        u[1] = P.U[1] + P.W[2] * d[0] - P.W[0] * d[2];
+        u[2] = P.U[2] + P.W[0] * d[1] - P.W[1] * d[0];
     }
-    const double uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
+    const double e0 = (rho - rho0) - 1.5 * rho * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
+    // site offsets of the neighbours at +1 and -1 along each axis
+    const int dx[2] = {x == nx - 1 ? 1 - nx : 1, x == 0 ? nx - 1 : -1};
+    const int dy[2] = {(y == ny - 1 ? 1 - ny : 1) * nx, (y == 0 ? ny - 1 : -1) * nx};
+    const int dz[2] = {(z == nz - 1 ? 1 - nz : 1) * nx * ny, (z == 0 ? nz - 1 : -1) * nx * ny};
     typename S::T* fb = f + B.foff;
+    auto put = [&](int i, double dev) {
+        // the slot this node reads f_i from at the next step (no walls here)
+        const int to = CV == CV_ODD ? 0 : (cx(i) ? dx[cx(i) > 0] : 0) + (cy(i) ? dy[cy(i) > 0] : 0) +
+                                              (cz(i) ? dz[cz(i) > 0] : 0);
+        S::st64(fb + (long long)(CV == CV_EVEN ? opp(i) : i) * B.stride + (s + to), dev, kp.scale);
+    };
+    put(0, wgt<Q>(0) * e0);
 #pragma unroll
-    for (int i = 0; i < Q; ++i) {
+    for (int i = 1; i < Q; i += 2) {
         const double cu = cx(i) * u[0] + cy(i) * u[1] + cz(i) * u[2];
-        const double dev = wgt<Q>(i) * ((rho - rho0) + rho * (3.0 * cu + 4.5 * cu * cu - 1.5 * uu));
-        // the slot node (x, y, z) reads f_i from at the next step (no walls here)
-        int d, slot;
-        pre_slot_open(kp.conv, i, x, y, z, nx, ny, nz, d, slot);
-        S::st64(fb + (long long)d * B.stride + slot, dev, kp.scale);
+        const double ev = wgt<Q>(i) * (e0 + 4.5 * rho * cu * cu), od = wgt<Q>(i) * (3.0 * rho * cu);
+        put(i, ev + od);
+        put(i + 1, ev - od);
     }
 }
 
@@ -913,49 +1151,87 @@ hipError_t launch_warm_targets(const PartDev* parts, int np, const double* s, do
     return hipGetLastError();
 }
 
-size_t stokes_scratch_doubles(int nboxes, int ntiles) {
-    return (size_t)nboxes * WM * MC * 2 + (size_t)ntiles * NPART + 4 * (size_t)nboxes;
+// Planes of a box are dealt to slabs of about 8192 nodes (1 to 512 of them, no
+// more than planes): enough work-groups for one large box, a few sums to add
+// for a small one.  A function of the box alone, so a box's sums do not depend on
+// what else is started.
+int stokes_slabs(int nx, int ny, int nz) {
+    const long long n = (long long)nx * ny * nz;
+    return (int)std::max<long long>(1, std::min<long long>(std::min<long long>(nz, 512), n / 8192));
+}
+
+void stokes_tile(int nx, int ny, int& rows, int& planes) {
+    rows = std::max(rows, tile_rows(nx));
+    planes = std::max(planes, tile_planes(nx, ny));
+}
+
+namespace {
+struct StokesScratch {  // offsets in doubles
+    size_t S, C, partial, ubar, fc, pbox, total;
+};
+StokesScratch stokes_layout(int nboxes, int ntiles, int nslabs, int max_particles) {
+    StokesScratch L{};
+    size_t at = 0;
+    auto take = [&](size_t n) {
+        const size_t o = at;
+        at += n;
+        return o;
+    };
+    L.S = take((size_t)nslabs * SLAB);
+    L.C = take((size_t)nboxes * WM * MC);
+    L.partial = take((size_t)ntiles * NPART);
+    L.ubar = take(4 * (size_t)nboxes);
+    L.fc = take((size_t)max_particles * FLOW_DOUBLES);
+    L.pbox = take(((size_t)max_particles + 1) / 2);
+    L.total = at;
+    return L;
+}
+}  // namespace
+
+size_t stokes_scratch_doubles(int nboxes, int ntiles, int nslabs, int max_particles) {
+    return stokes_layout(nboxes, ntiles, nslabs, max_particles).total;
 }
 int stokes_free_doubles() { return UF; }
 
-hipError_t launch_stokes_start(const BoxDesc* boxes, int nboxes, const int* tile_box, int ntiles,
-                               const uint16_t* omap, const PartDev* parts, int np, double mu, double* scratch,
-                               double* uf, long long base, void* f, const KParams& kp, int only_box, hipStream_t st) {
-    double* S = scratch;
-    double* C = S + (size_t)nboxes * WM * MC;
-    double* partial = C + (size_t)nboxes * WM * MC;
-    double* ubar = partial + (size_t)ntiles * NPART;
-    hipLaunchKernelGGL(k_stokes_free, dim3(ntiles), dim3(TILE), 0, st, boxes, tile_box, parts, np, mu, only_box, base,
+hipError_t launch_stokes_start(const BoxDesc* boxes, int nboxes, const int* tile_box, int ntiles, int nslabs,
+                               int box_slabs, int rows, int planes, int max_particles, const uint16_t* omap,
+                               const PartDev* parts, int np, double mu, double* scratch, double* uf, long long base,
+                               void* f, const KParams& kp, int only_box, hipStream_t st) {
+    const StokesScratch L = stokes_layout(nboxes, ntiles, nslabs, max_particles);
+    double *S = scratch + L.S, *C = scratch + L.C, *partial = scratch + L.partial, *ubar = scratch + L.ubar;
+    FlowConst* fc = reinterpret_cast<FlowConst*>(scratch + L.fc);
+    int* pbox = reinterpret_cast<int*>(scratch + L.pbox);
+    if (np > 0)
+        hipLaunchKernelGGL(k_stokes_prep, dim3((np + 63) / 64), dim3(64), 0, st, parts, np, mu, fc, pbox);
+    hipLaunchKernelGGL(k_stokes_free, dim3(ntiles), dim3(TILE), 0, st, boxes, tile_box, fc, pbox, np, only_box, base,
                        uf);
-    hipLaunchKernelGGL(k_stokes_modes, dim3((2 * WK + 1) * (2 * WK + 1) * nboxes), dim3(256), 0, st, boxes, uf, base,
-                       only_box, S);
-    hipLaunchKernelGGL(k_stokes_coef, dim3((nboxes * WM + 127) / 128), dim3(128), 0, st, boxes, nboxes, parts, np, mu,
-                       S, C);
-    hipLaunchKernelGGL(k_stokes_sum, dim3(ntiles), dim3(TILE), 0, st, boxes, tile_box, omap, parts, uf, base,
-                       only_box, C, partial);
-    hipLaunchKernelGGL(k_stokes_mean, dim3(nboxes), dim3(64), 0, st, boxes, parts, np, partial, kp.rho0, ubar);
-    auto write = [&](auto q) {
-        constexpr int Q = decltype(q)::value;
-        switch (kp.storage) {
-            case ST_F64:
-                hipLaunchKernelGGL((k_stokes_write<ST_F64, Q>), dim3(ntiles), dim3(TILE), 0, st, boxes, tile_box,
-                                   omap, parts, uf, base, C, ubar, (double*)f, kp, only_box);
-                break;
-            case ST_F32:
-                hipLaunchKernelGGL((k_stokes_write<ST_F32, Q>), dim3(ntiles), dim3(TILE), 0, st, boxes, tile_box,
-                                   omap, parts, uf, base, C, ubar, (float*)f, kp, only_box);
-                break;
-            case ST_F16:
-                hipLaunchKernelGGL((k_stokes_write<ST_F16, Q>), dim3(ntiles), dim3(TILE), 0, st, boxes, tile_box,
-                                   omap, parts, uf, base, C, ubar, (typename Store<ST_F16>::T*)f, kp, only_box);
-                break;
-            default:
-                hipLaunchKernelGGL((k_stokes_write<ST_BF16, Q>), dim3(ntiles), dim3(TILE), 0, st, boxes, tile_box,
-                                   omap, parts, uf, base, C, ubar, (typename Store<ST_BF16>::T*)f, kp, only_box);
-        }
+    hipLaunchKernelGGL(k_stokes_modes, dim3(box_slabs * nboxes), dim3(256), 0, st, boxes, uf, base, only_box, box_slabs,
+                       S);
+    hipLaunchKernelGGL(k_stokes_coef, dim3(nboxes), dim3(128), 0, st, boxes, parts, pbox, np, mu, only_box, S, C);
+    hipLaunchKernelGGL(k_stokes_sum, dim3(ntiles), dim3(TILE),
+                       sizeof(double) * ((size_t)planes * PLANE_DOUBLES + (size_t)rows * ROW_DOUBLES), st, boxes,
+                       tile_box, omap, uf, base, only_box, C, planes, partial);
+    hipLaunchKernelGGL(k_stokes_mean, dim3(nboxes), dim3(256), 0, st, boxes, parts, np, partial, kp.rho0, ubar);
+    auto write = [&](auto st_, auto q_, auto cv_) {
+        constexpr int ST = decltype(st_)::value, Q = decltype(q_)::value, CV = decltype(cv_)::value;
+        hipLaunchKernelGGL((k_stokes_write<ST, Q, CV>), dim3(ntiles), dim3(TILE), 0, st, boxes, tile_box, omap, parts,
+                           uf, base, ubar, (typename Store<ST>::T*)f, kp, only_box);
     };
-    if (kp.q == 27) write(std::integral_constant<int, 27>{});
-    else write(std::integral_constant<int, 19>{});
+    auto by_cv = [&](auto st_, auto q_) {
+        if (kp.conv == CV_ODD) write(st_, q_, std::integral_constant<int, CV_ODD>{});
+        else if (kp.conv == CV_EVEN) write(st_, q_, std::integral_constant<int, CV_EVEN>{});
+        else write(st_, q_, std::integral_constant<int, CV_PULL>{});
+    };
+    auto by_q = [&](auto st_) {
+        if (kp.q == 27) by_cv(st_, std::integral_constant<int, 27>{});
+        else by_cv(st_, std::integral_constant<int, 19>{});
+    };
+    switch (kp.storage) {
+        case ST_F64: by_q(std::integral_constant<int, ST_F64>{}); break;
+        case ST_F32: by_q(std::integral_constant<int, ST_F32>{}); break;
+        case ST_F16: by_q(std::integral_constant<int, ST_F16>{}); break;
+        default: by_q(std::integral_constant<int, ST_BF16>{});
+    }
     return hipGetLastError();
 }
 

@@ -38,6 +38,9 @@ struct Layout {
     std::vector<int> tile0, ntiles;
     long long pop_elems = 0, omap_elems = 0, link_pool = 0;
     int total_tiles = 0, max_particles = 0, lds_words = 0;
+    std::vector<int> slab0, nslab;
+    int total_slabs = 0, box_slabs = 0;  // of the start field's Fourier sums: over all boxes, the largest of one
+    int tile_rows = 0, tile_planes = 0;  // rows and planes a 256-site tile can touch
     size_t scratch_bytes = 0;
 };
 
@@ -105,6 +108,11 @@ Layout make_layout(const lb_config* c, int nboxes, const lb_box* boxes) {
         L.tile0.push_back(tiles);
         L.ntiles.push_back(nt);
         tiles += nt;
+        L.slab0.push_back(L.total_slabs);
+        L.nslab.push_back(stokes_slabs(boxes[b].nx, boxes[b].ny, boxes[b].nz));
+        L.total_slabs += L.nslab[b];
+        L.box_slabs = std::max(L.box_slabs, L.nslab[b]);
+        stokes_tile(boxes[b].nx, boxes[b].ny, L.tile_rows, L.tile_planes);
         maxpart = std::max(maxpart, (size_t)((n + TILE - 1) / TILE) * 6 * sizeof(double));
         L.coff.push_back(L.cells);
         L.cells += (long long)((boxes[b].nx + 7) / 8) * ((boxes[b].ny + 7) / 8) * ((boxes[b].nz + 7) / 8);
@@ -145,7 +153,7 @@ Layout make_layout(const lb_config* c, int nboxes, const lb_box* boxes) {
     L.step_ctr = take(sizeof(uint32_t) * 4);
     // warm start: per particle load scale (1), prediction (6) and training
     // sample (8 + 6 floats = 7 doubles); then the start field's scratch
-    L.warm = take(sizeof(double) * (14 * (size_t)L.max_particles + stokes_scratch_doubles(nboxes, tiles)));
+    L.warm = take(sizeof(double) * (14 * (size_t)L.max_particles + stokes_scratch_doubles(nboxes, tiles, L.total_slabs, L.max_particles)));
     // boxes with several particles: owner-change stamps per cell of 8^3
     // nodes, and each particle's remap claim candidates (one window bitmask)
     L.stamps = take(sizeof(uint32_t) * (size_t)L.cells);
@@ -487,6 +495,8 @@ lb_status lb_init(const lb_config* cfg, int nboxes, const lb_box* boxes, void* d
         D.coff = ctx->L.coff[b];
         D.cnx = (X.nx + 7) / 8;
         D.cny = (X.ny + 7) / 8;
+        D.slab0 = ctx->L.slab0[b];
+        D.nslab = ctx->L.nslab[b];
         for (int k = 0; k < 3; ++k) {
             D.wall_lo[k] = X.wall_lo[k];
             D.wall_hi[k] = X.wall_hi[k];
@@ -1409,9 +1419,11 @@ lb_status stokes_start(lb_ctx* ctx, int only_box = -1) {
         return fail(ctx, LB_EINVAL, "population buffer too small for the start field's scratch");
     }
     HIPC(launch_stokes_start(ctx->at<BoxDesc>(ctx->L.boxes), (int)ctx->boxes.size(), ctx->at<int>(ctx->L.tile_box),
-                             ctx->L.total_tiles, ctx->at<uint16_t>(ctx->L.omap), ctx->at<PartDev>(ctx->L.parts),
-                             ctx->np, viscosity(ctx) * ctx->kp.rho0, scratch, (double*)spare, base,
-                             ctx->fbuf(ctx->cur), ctx->kp, only_box, ctx->stream));
+                             ctx->L.total_tiles, ctx->L.total_slabs, ctx->L.box_slabs, ctx->L.tile_rows,
+                             ctx->L.tile_planes, ctx->L.max_particles,
+                             ctx->at<uint16_t>(ctx->L.omap), ctx->at<PartDev>(ctx->L.parts), ctx->np,
+                             viscosity(ctx) * ctx->kp.rho0, scratch, (double*)spare, base, ctx->fbuf(ctx->cur),
+                             ctx->kp, only_box, ctx->stream));
     return LB_OK;
 }
 }  // namespace

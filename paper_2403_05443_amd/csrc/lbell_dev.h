@@ -91,6 +91,7 @@ struct BoxDesc {
     int lnx, lny;
     long long coff;       // offset of the box's cells (8^3 nodes each) in the owner-change stamps
     int cnx, cny;         // cells along x and y
+    int slab0, nslab;     // partial sums of the start field's Fourier modes: first, count
 };
 
 // Division of 0 <= n < 2^27 (a site index, SITE_BITS) by d >= 1 as one

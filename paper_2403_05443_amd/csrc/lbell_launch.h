@@ -133,14 +133,20 @@ hipError_t launch_warm_features(const BoxDesc* boxes, const PartDev* parts, int 
 hipError_t launch_warm_apply(PartDev* parts, int np, const float* Y, const double* s, double mu, double* pred,
                              int only_box, hipStream_t st);
 hipError_t launch_warm_targets(const PartDev* parts, int np, const double* s, double mu, float* Y, hipStream_t st);
-size_t stokes_scratch_doubles(int nboxes, int ntiles);  // scratch of launch_stokes_start
+int stokes_slabs(int nx, int ny, int nz);  // work-groups (and partial sums) of a box's Fourier sums
+// raises rows and planes to what a 256-site tile of an nx x ny x nz box can touch
+void stokes_tile(int nx, int ny, int& rows, int& planes);
+size_t stokes_scratch_doubles(int nboxes, int ntiles, int nslabs, int max_particles);  // scratch of launch_stokes_start
 int stokes_free_doubles();  // doubles per node of its staged free field (uf)
-// only_box >= 0: that box only (every box otherwise).  uf: stokes_free_doubles()
-// doubles per node of the started boxes, node (box B, site s) at that many
+// nslabs: over all boxes; box_slabs: the largest of one box; rows, planes: of
+// stokes_tile over the boxes.  only_box >= 0:
+// that box only (every box otherwise).  uf: stokes_free_doubles() doubles per
+// node of the started boxes (16-byte aligned), node (box B, site s) at that many
 // times (B.ooff + s - base).
-hipError_t launch_stokes_start(const BoxDesc* boxes, int nboxes, const int* tile_box, int ntiles,
-                               const uint16_t* omap, const PartDev* parts, int np, double mu, double* scratch,
-                               double* uf, long long base, void* f, const KParams& kp, int only_box, hipStream_t st);
+hipError_t launch_stokes_start(const BoxDesc* boxes, int nboxes, const int* tile_box, int ntiles, int nslabs,
+                               int box_slabs, int rows, int planes, int max_particles, const uint16_t* omap,
+                               const PartDev* parts, int np, double mu, double* scratch, double* uf, long long base,
+                               void* f, const KParams& kp, int only_box, hipStream_t st);
 // ---- fallback monitor of warm-started boxes ----
 // per tile: sum over fluid sites of |j|^2 for boxes whose monitor is pending (k_stream.hip)
 hipError_t launch_box_energy(const BoxDesc* boxes, const int* tile_box, int ntiles, const uint16_t* omap,

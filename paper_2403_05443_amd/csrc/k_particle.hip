@@ -460,6 +460,8 @@ __device__ __forceinline__ void mark_near(const NearSet& ns, const BoxDesc& B, c
     }
 }
 
+constexpr int MAXSEG = 64;  // segments of 4096 nodes of the largest window (7168 words of 32 nodes: 56)
+
 struct SolveShm {
     double red[12][PWAVES];
     double bc[8];
@@ -866,14 +868,13 @@ __device__ __forceinline__ void solve_phase(const LaunchPart& a, int p, PartDev&
     }
 }
 
-constexpr int P2B = 8;  // windows of up to P2B chunks of PBLOCK nodes take the batched link pass
-
 struct RemapShm {
     double red[15][PWAVES];
     double mred[PWAVES];
     int wtot[PWAVES];
     int ired[8][PWAVES];
-    int wchunk[P2B][PWAVES];  // links per wave and chunk (batched link pass)
+    int wchunk[4][PWAVES];  // links per wave and group of listed nodes (link pass)
+    int segcnt[MAXSEG];     // links per SEG window nodes (link pass)
 };
 
 // Whether the window must be tested again.  At its last test every node of
@@ -1608,10 +1609,54 @@ __device__ __forceinline__ void claim_pass(const LaunchPart& a, int p, PartDev& 
 }
 
 
+// The window nodes of word wi (32 nodes from 32 wi) that are not solid and
+// have a solid neighbour in the velocity set: the solid bits of the nine
+// neighbouring rows, shifted by -1, 0 or 1 along x.  Only for windows that do not
+// span a whole axis: their outermost layers hold no solid node, so a shift
+// across the end of a row or plane reads zeros.  bits beyond the window are zero.
+template <int Q>
+__device__ __forceinline__ uint32_t shell_word(const uint32_t* bits, int nwords, int wi, int wx, int wxy) {
+    uint32_t any = 0;
+    auto word = [&](int k) { return (unsigned)k < (unsigned)nwords ? bits[k] : 0u; };
+#pragma unroll
+    for (int dz = -1; dz <= 1; ++dz)
+#pragma unroll
+        for (int dy = -1; dy <= 1; ++dy) {
+            // node 32 wi + dy wx + dz wxy - 1 is bit `off` of word k
+            const int n0 = 32 * wi + dy * wx + dz * wxy - 1, k = n0 >> 5, off = n0 & 31;
+            const uint32_t w0 = word(k), w1 = word(k + 1), w2 = word(k + 2);
+            auto at = [&](int o) {  // the 32 bits from bit o of (w2, w1, w0)
+                return o < 32 ? __builtin_amdgcn_alignbit(w1, w0, o) : __builtin_amdgcn_alignbit(w2, w1, o - 32);
+            };
+            if (!(dy && dz)) {
+                any |= at(off) | at(off + 2);       // (-1, dy, dz), (1, dy, dz)
+                if (dy || dz) any |= at(off + 1);   // (0, dy, dz)
+            } else {
+                any |= at(off + 1);
+                if (Q == 27) any |= at(off) | at(off + 2);
+            }
+        }
+    return any & ~bits[wi];
+}
+
 // Pass 2: the boundary links (fluid x, x + c_b solid of this particle; bits
 // holds this particle's nodes over the window), staged in LDS and written in
 // (window index, direction) order, and their moments, from which zeta of
 // eqs. drag1-drag4 is evaluated when the next step starts.
+//
+// Bound by latency and by how evenly the work falls on the lanes.  The nodes
+// that can carry a link are the shell around the body, found 32 at a time
+// from the bit mask (shell_word) and listed in index order, KLINK * PBLOCK at
+// a time (2 a lane hold the ~800 of a (20, 4, 4) spheroid in one round): their
+// node-map loads and neighbour tests then take every lane, and the barriers
+// do not grow with the window.  Walking the window in chunks of PBLOCK nodes
+// took three barriers a chunk beyond eight chunks and left most lanes without
+// a link: k_particle_links on 512 squirmers 26.7 -> 23.6 us, the slowest
+// rebuild of the 256-box ensemble's step 150 -> 90 us, set-up's
+// k_particle_remap there 66 -> 43 us.
+constexpr int KLINK = 2;
+constexpr int SEG = 4096;  // window nodes whose moments are summed at a time (their masks fit the stage)
+static_assert(SEG <= STAGE && SEG % PBLOCK == 0, "the masks lie over the stage");
 template <int Q>
 __device__ __forceinline__ void link_pass(const LaunchPart& a, int p, const PartDev& P, const BoxDesc& B, const Win& w,
                           const uint32_t* bits, uint32_t* stage, RemapShm& sh) {
@@ -1624,177 +1669,183 @@ __device__ __forceinline__ void link_pass(const LaunchPart& a, int p, const Part
     const int lane = tid & 63, wv = tid >> 6;
     const double xc[3] = {P.xc[0], P.xc[1], P.xc[2]};
     const int nsites = w.nsites;
-    const int* lo = w.lo;
     const int* wn = w.wn;
     const bool* whole = w.whole;
-    const double rw0 = w.rw0, rw1 = w.rw1;
 
-    ZAcc<Q> z;
-    z.clear();
     int running = 0;
     const int lcap = P.lcap;
     uint32_t* L = a.links + P.lbase;
-    // the link mask of window node i: bit b set when i is fluid and i + c_b
-    // is solid here (the node map is read only where bits[] says not this
-    // particle's)
-    auto link_mask = [&](int i, uint16_t own, int& s, int& gx, int& gy, int& gz) -> uint32_t {
-        uint32_t lm = 0;
-        int wx, wy;
-        const int wz = divmod(divmod(i, wn[0], rw0, wx), wn[1], rw1, wy);
-        gx = wrap(lo[0] + wx, nx);
-        gy = wrap(lo[1] + wy, ny);
-        gz = wrap(lo[2] + wz, nz);
-        s = gx + nx * (gy + ny * gz);
-        if (own == 0) {
-#pragma unroll
-            for (int b = 1; b < Q; ++b) {
-                int nwx = wx + cx(b), nwy = wy + cy(b), nwz = wz + cz(b);
-                if (whole[0]) nwx = wrap(nwx, wn[0]);
-                else if (nwx < 0 || nwx >= wn[0]) continue;
-                if (whole[1]) nwy = wrap(nwy, wn[1]);
-                else if (nwy < 0 || nwy >= wn[1]) continue;
-                if (whole[2]) nwz = wrap(nwz, wn[2]);
-                else if (nwz < 0 || nwz >= wn[2]) continue;
-                const int ni = nwx + wn[0] * (nwy + wn[1] * nwz);
-                if ((bits[ni >> 5] >> (ni & 31)) & 1u) lm |= 1u << b;
-            }
-        }
-        return lm;
+
+    // candidate nodes: the shell, or, in a window that spans an axis, every
+    // node that is not solid
+    const bool wraps = whole[0] || whole[1] || whole[2];
+    const int nwords = (nsites + 31) >> 5, wx1 = wn[0], wxy = wn[0] * wn[1];
+    const int per = (nwords + PBLOCK - 1) / PBLOCK;  // consecutive words per thread
+    auto cand_word = [&](int wi) -> uint32_t {
+        const uint32_t m = wraps ? ~bits[wi] : shell_word<Q>(bits, nwords, wi, wx1, wxy);
+        const int left = nsites - 32 * wi;
+        return left >= 32 ? m : m & ((1u << left) - 1u);
     };
-    const int nch = (nsites + PBLOCK - 1) / PBLOCK;
-    if (nch <= P2B) {
-        // small windows: every chunk's masks first (the node-map loads of all
-        // chunks in flight together), one block scan over all chunks, one
-        // staged copy-out; same order and same sums as below
-        uint32_t lmv[P2B];
-        int sv[P2B], offv[P2B];
-        uint16_t ownv[P2B];
-#pragma unroll
-        for (int c = 0; c < P2B; ++c) {
-            const int i = c * PBLOCK + tid;
-            ownv[c] = 1;  // not fluid
-            if (i < nsites && !((bits[i >> 5] >> (i & 31)) & 1u)) {
-                int wx, wy;
-                const int wz = divmod(divmod(i, wn[0], rw0, wx), wn[1], rw1, wy);
-                ownv[c] = om[wrap(lo[0] + wx, nx) + nx * (wrap(lo[1] + wy, ny) + ny * wrap(lo[2] + wz, nz))];
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < P2B; ++c) {
-            lmv[c] = 0;
-            sv[c] = 0;
-            offv[c] = 0;
-            if (c < nch) {  // uniform over the block
-                const int i = c * PBLOCK + tid;
-                int gx = 0, gy = 0, gz = 0;
-                if (i < nsites) lmv[c] = link_mask(i, ownv[c], sv[c], gx, gy, gz);
-                uint32_t mm = lmv[c];
-                while (mm) {
-                    const int b = __ffs(mm) - 1;
-                    mm &= mm - 1;
-                    z.add(b, gx, gy, gz, xc, nx, ny, nz);
+    if (tid < MAXSEG) sh.segcnt[tid] = 0;
+    int cnt = 0;
+    uint32_t first = 0;  // the thread's first word, kept for the listing
+    for (int j = 0; j < per; ++j) {
+        const int wi = tid * per + j;
+        const uint32_t m = wi < nwords ? cand_word(wi) : 0u;
+        if (j == 0) first = m;
+        cnt += __popc(m);
+    }
+    int incl = cnt;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(incl, o);
+        if (lane >= o) incl += t;
+    }
+    if (lane == 63) wtot[wv] = incl;
+    __syncthreads();
+    int base = incl - cnt, nc = 0;
+    for (int v = 0; v < PWAVES; ++v) {
+        const int t = wtot[v];
+        if (v < wv) base += t;
+        nc += t;
+    }
+
+    for (int r0 = 0; r0 < nc; r0 += KLINK * PBLOCK) {
+        const int r1 = min(nc, r0 + KLINK * PBLOCK);
+        if (base < r1 && base + cnt > r0) {
+            int o = base;
+            for (int j = 0; j < per; ++j) {
+                const int wi = tid * per + j;
+                uint32_t m = j == 0 ? first : (wi < nwords ? cand_word(wi) : 0u);
+                while (m) {
+                    const int bt = __ffs(m) - 1;
+                    m &= m - 1;
+                    if (o >= r0 && o < r1) stage[o - r0] = (uint32_t)(wi * 32 + bt);
+                    ++o;
                 }
-                const int cnt = __popc(lmv[c]);
-                int incl = cnt;
-                for (int o = 1; o < 64; o <<= 1) {
-                    const int nb = __shfl_up(incl, o);
-                    if (lane >= o) incl += nb;
-                }
-                offv[c] = incl - cnt;
-                if (lane == 63) sh.wchunk[c][wv] = incl;
             }
         }
         __syncthreads();
+        // link masks of the listed nodes: bit b set when the node is fluid and
+        // its neighbour along c_b is solid here
+        int ni_[KLINK], wi_[KLINK][3], sv[KLINK], offv[KLINK];
+        uint32_t lmv[KLINK];
+        uint16_t own[KLINK];
+#pragma unroll
+        for (int c = 0; c < KLINK; ++c) {
+            const int k = r0 + c * PBLOCK + tid;
+            own[c] = 1;  // not fluid
+            sv[c] = 0;
+            if (k < r1) {
+                const int i = (int)stage[k - r0];
+                ni_[c] = i;
+                wi_[c][2] = divmod(divmod(i, wn[0], w.rw0, wi_[c][0]), wn[1], w.rw1, wi_[c][1]);
+                sv[c] = wrap(w.lo[0] + wi_[c][0], nx) +
+                        nx * (wrap(w.lo[1] + wi_[c][1], ny) + ny * wrap(w.lo[2] + wi_[c][2], nz));
+                own[c] = om[sv[c]];
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < KLINK; ++c) {
+            uint32_t lm = 0;
+            if (own[c] == 0) {
+#pragma unroll
+                for (int b = 1; b < Q; ++b) {
+                    int nwx = wi_[c][0] + cx(b), nwy = wi_[c][1] + cy(b), nwz = wi_[c][2] + cz(b);
+                    if (whole[0]) nwx = wrap(nwx, wn[0]);
+                    else if (nwx < 0 || nwx >= wn[0]) continue;
+                    if (whole[1]) nwy = wrap(nwy, wn[1]);
+                    else if (nwy < 0 || nwy >= wn[1]) continue;
+                    if (whole[2]) nwz = wrap(nwz, wn[2]);
+                    else if (nwz < 0 || nwz >= wn[2]) continue;
+                    const int ni = nwx + wn[0] * (nwy + wn[1] * nwz);
+                    if ((bits[ni >> 5] >> (ni & 31)) & 1u) lm |= 1u << b;
+                }
+            }
+            lmv[c] = lm;
+            const int nl = __popc(lm);
+            if (nl) atomicAdd(&sh.segcnt[ni_[c] / SEG], nl);
+            int in2 = nl;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int t = __shfl_up(in2, o);
+                if (lane >= o) in2 += t;
+            }
+            offv[c] = in2 - nl;
+            if (lane == 63) sh.wchunk[c][wv] = in2;
+        }
+        __syncthreads();  // also: the list has been read
         int total = 0;
 #pragma unroll
-        for (int c = 0; c < P2B; ++c) {
-            if (c < nch) {
-                int before = 0, all = 0;
-                for (int v = 0; v < PWAVES; ++v) {
-                    const int t = sh.wchunk[c][v];
-                    if (v < wv) before += t;
-                    all += t;
-                }
-                offv[c] += total + before;
-                total += all;
-            }
-        }
-        if (total <= STAGE) {
-#pragma unroll
-            for (int c = 0; c < P2B; ++c) {
-                uint32_t m2 = lmv[c];
-                int idx = offv[c];
-                while (m2) {
-                    const int b = __ffs(m2) - 1;
-                    m2 &= m2 - 1;
-                    stage[idx++] = (uint32_t)sv[c] | ((uint32_t)b << SITE_BITS);
-                }
-            }
-            __syncthreads();
-            for (int j = tid; j < total; j += PBLOCK)
-                if (j < lcap) L[j] = stage[j];
-        } else {  // more links than the stage holds: each thread writes its own
-#pragma unroll
-            for (int c = 0; c < P2B; ++c) {
-                uint32_t m2 = lmv[c];
-                int idx = offv[c];
-                while (m2) {
-                    const int b = __ffs(m2) - 1;
-                    m2 &= m2 - 1;
-                    if (idx < lcap) L[idx] = (uint32_t)sv[c] | ((uint32_t)b << SITE_BITS);
-                    ++idx;
-                }
-            }
-        }
-        running = total;
-    } else {
-        for (int base = 0; base < nsites; base += PBLOCK) {
-            const int i = base + tid;
-            uint32_t lm = 0;
-            int s = 0, gx = 0, gy = 0, gz = 0;
-            if (i < nsites && !((bits[i >> 5] >> (i & 31)) & 1u)) {
-                int wx, wy;
-                const int wz = divmod(divmod(i, wn[0], rw0, wx), wn[1], rw1, wy);
-                const uint16_t own = om[wrap(lo[0] + wx, nx) + nx * (wrap(lo[1] + wy, ny) + ny * wrap(lo[2] + wz, nz))];
-                lm = link_mask(i, own, s, gx, gy, gz);
-            }
-            const int cnt = __popc(lm);
-            int incl = cnt;
-            for (int o = 1; o < 64; o <<= 1) {
-                const int nb = __shfl_up(incl, o);
-                if (lane >= o) incl += nb;
-            }
-            if (lane == 63) wtot[wv] = incl;
-            __syncthreads();
-            int off = incl - cnt, total = 0;
+        for (int c = 0; c < KLINK; ++c) {
             for (int v = 0; v < PWAVES; ++v) {
-                if (v < wv) off += wtot[v];
-                total += wtot[v];
+                if (v == wv) offv[c] += total;
+                total += sh.wchunk[c][v];
             }
-            uint32_t mm = lm;
-            while (mm) {
-                const int b = __ffs(mm) - 1;
-                mm &= mm - 1;
-                z.add(b, gx, gy, gz, xc, nx, ny, nz);
-            }
-            for (int r0 = 0; r0 < total; r0 += STAGE) {
-                uint32_t m2 = lm;
-                int idx = off;
+        }
+        for (int s0 = 0; s0 < total; s0 += STAGE) {
+#pragma unroll
+            for (int c = 0; c < KLINK; ++c) {
+                uint32_t m2 = lmv[c];
+                int idx = offv[c] - s0;
                 while (m2) {
                     const int b = __ffs(m2) - 1;
                     m2 &= m2 - 1;
-                    if (idx >= r0 && idx < r0 + STAGE) stage[idx - r0] = (uint32_t)s | ((uint32_t)b << SITE_BITS);
+                    if ((unsigned)idx < (unsigned)STAGE) stage[idx] = (uint32_t)sv[c] | ((uint32_t)b << SITE_BITS);
                     ++idx;
                 }
-                __syncthreads();
-                const int n_r = min(STAGE, total - r0);
-                for (int j = tid; j < n_r; j += PBLOCK) {
-                    const int dst = running + r0 + j;
-                    if (dst < lcap) L[dst] = stage[j];
-                }
-                __syncthreads();
             }
-            running += total;
+            __syncthreads();
+            const int n_r = min(STAGE, total - s0);
+            for (int j = tid; j < n_r; j += PBLOCK) {
+                const int dst = running + s0 + j;
+                if (dst < lcap) L[dst] = stage[j];
+            }
+            if (s0 + STAGE < total || r1 < nc) __syncthreads();  // before the next codes or list
+        }
+        running += total;
+    }
+    // the moments, SEG window nodes at a time: the links' direction masks go
+    // back to their nodes' places (LDS, over the stage), and lane i mod PBLOCK
+    // takes node i, so that the sums' order is that of the window whatever the
+    // listing; a lane runs through all its links in one loop
+    ZAcc<Q> z;
+    z.clear();
+    constexpr int SEG_N = SEG / PBLOCK;
+    int c0 = 0;  // first link of the segment
+    for (int g0 = 0; g0 < nsites && c0 < running; g0 += SEG) {
+        const int nseg = sh.segcnt[g0 / SEG];
+        if (nseg == 0) continue;  // uniform over the block
+        __syncthreads();  // the stage, or the previous segment's masks, have been read; L is written
+        for (int k = tid; k < SEG; k += PBLOCK) stage[k] = 0u;
+        __syncthreads();
+        const int c1 = min(c0 + nseg, lcap);
+        for (int j = c0 + tid; j < c1; j += PBLOCK) {
+            const uint32_t code = L[j];
+            int x, y;
+            const int zz = div_magic(div_magic((int)(code & SITE_MASK), nx, B.mnx, B.lnx, x), ny, B.mny, B.lny, y);
+            const int i = wrap(x - w.lo[0], nx) + wn[0] * (wrap(y - w.lo[1], ny) + wn[1] * wrap(zz - w.lo[2], nz));
+            atomicOr(&stage[i - g0], 1u << (code >> SITE_BITS));
+        }
+        c0 += nseg;
+        __syncthreads();
+        uint32_t lm[SEG_N], mm = 0;
+        int left = 0;
+#pragma unroll
+        for (int k = 0; k < SEG_N; ++k) {
+            lm[k] = stage[k * PBLOCK + tid];
+            left |= lm[k] ? 1 << k : 0;
+        }
+        int gx = 0, gy = 0, gz = 0;
+        while (mm || left) {
+            if (!mm) {
+                const int k = __ffs(left) - 1;
+                left &= left - 1;
+#pragma unroll
+                for (int v = 0; v < SEG_N; ++v) mm = v == k ? lm[v] : mm;
+                win_node(w, B, g0 + k * PBLOCK + tid, gx, gy, gz);
+            }
+            const int b = __ffs(mm) - 1;
+            mm &= mm - 1;
+            z.add(b, gx, gy, gz, xc, nx, ny, nz);
         }
     }
     if (running > lcap && tid == 0) atomicOr(a.flags, (int)F_LINKS);

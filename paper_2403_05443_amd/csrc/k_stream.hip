@@ -571,7 +571,9 @@ __global__ __launch_bounds__(256) void k_collide_stream_rows(const BoxDesc* __re
 
 // Initial state: every slot holds the pre-collision population its reader
 // pulls at the first step, f_eq(rho0, u0) plus the first-order
-// non-equilibrium part of the Couette profile (zero at rest).
+// non-equilibrium part of the Couette profile (zero at rest).  f1: the second
+// buffer of the pull layout, or null (one buffer, in the layout of an even
+// in-place step: the directions swapped).
 template <int ST, int Q>
 __global__ __launch_bounds__(TILE) void k_init(const BoxDesc* __restrict__ boxes,
                                                const int* __restrict__ tile_box,
@@ -621,8 +623,8 @@ __global__ __launch_bounds__(TILE) void k_init(const BoxDesc* __restrict__ boxes
         (void)nz;
         (void)x;
         (void)z;
-        S::st64(f0 + B.foff + (long long)i * B.stride + s, val, kp.scale);
-        S::st64(f1 + B.foff + (long long)i * B.stride + s, val, kp.scale);
+        S::st64(f0 + B.foff + (long long)(kp.conv == CV_EVEN ? opp(i) : i) * B.stride + s, val, kp.scale);
+        if (f1) S::st64(f1 + B.foff + (long long)i * B.stride + s, val, kp.scale);
     }
 }
 

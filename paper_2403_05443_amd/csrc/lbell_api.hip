@@ -269,6 +269,33 @@ bool k1_applicable(const lb_ctx* ctx, int v) {
     return true;
 }
 
+// The variant a context starts with (all give the same bits; lb_autotune
+// measures them), by what one buffer of populations takes.  The times are per launch in
+// real steps, in us.
+//  - Two buffers fit the 256 MB last-level cache: pull, XCD-chunked (3): each
+//    XCD's L2 serves the cache lines its neighbouring tiles share.  96^3 FP32
+//    (67 MB) 18.2 against 19.2 in plain order (0) and 18.7 in place (12); 110^3 FP16 15.8,
+//    17.8, 16.9; 16 boxes of edges 32-64 in FP16 (74 MB) 21.3, 23.9, 22.0.
+//  - One buffer is worth keeping there: in place, XCD-chunked (12).  128^3
+//    FP32 (159 MB) 39 against 57 (0) and 59 (row-wave), 128^3 FP32 D3Q27 (226 MB) 55
+//    against 90, 160^3 FP16 (156 MB) 41 against 55; beyond the cache's size a share of
+//    it still hits: 160^3 FP32 (311 MB) 103 against 116 (15), 128^3 FP64
+//    (319 MB) 97 against 123.  At 442-453 MB (D3Q27) the two are level, at 538 MB
+//    pull wins, 191 against 212.  In the half formats it wins sooner, 192^3
+//    (269 MB) 94 against 107: the scattered stores are two bytes a lane.
+//  - Larger: pull in XCD-grouped order, non-temporal stores (15), 256^3 FP16 215 against 228
+//    (0) and 237 (row-wave), 256 boxes in FP16 368 against 382 (0); D3Q27 has
+//    no such kernel and takes the plain order (675 against 696 chunked, 256^3 FP32).
+// The two-stream schedule needs the plain order or the row-wave kernel.
+int initial_variant(const lb_ctx* ctx) {
+    if (ctx->overlap) return ctx->rows_k > 0 ? 1 : 0;
+    const int es = storage_bytes(ctx->cfg.storage);
+    const double mb = (double)ctx->L.pop_elems * es / 1e6;
+    if (2 * mb <= 256) return 3;
+    if (mb <= (es == 2 ? 200 : 400)) return 12;
+    return ctx->cfg.lattice == 27 ? 0 : 15;
+}
+
 lb_status fail(lb_ctx* c, lb_status s, const std::string& msg) {
     if (c) c->err = msg;
     return s;
@@ -427,10 +454,6 @@ size_t lb_arena_bytes(const lb_config* cfg, int nboxes, const lb_box* boxes) {
     return make_layout(cfg, nboxes, boxes).total;
 }
 
-namespace {
-lb_status switch_layout(lb_ctx* ctx, bool to_aa);
-}  // namespace
-
 lb_status lb_init(const lb_config* cfg, int nboxes, const lb_box* boxes, void* dev_arena, size_t arena_bytes,
                   void* hip_stream, lb_ctx** out) {
     if (!out) return LB_EINVAL;
@@ -471,6 +494,23 @@ lb_status lb_init(const lb_config* cfg, int nboxes, const lb_box* boxes, void* d
     }
     kp.scale = std::ldexp(1.0, e);
     kp.inv_scale = std::ldexp(1.0, -e);
+    if (nboxes == 1 && cfg->lattice == 19 && (boxes[0].nx == 64 || boxes[0].nx == 128 || boxes[0].nx == 256))
+        ctx->rows_k = boxes[0].nx / 64;
+    if (const char* v = std::getenv("LBELL_OVERLAP")) ctx->overlap = std::atoi(v) != 0;
+    if (const char* v = std::getenv("LBELL_FUSED")) ctx->fused = std::atoi(v) != 0;
+    if (const char* v = std::getenv("LBELL_BAND")) ctx->use_band = std::atoi(v) != 0;
+    ctx->k1_variant = initial_variant(ctx);
+    if (const char* v = std::getenv("LBELL_K1_VARIANT")) {
+        if (!k1_applicable(ctx, std::atoi(v))) {
+            std::fprintf(stderr, "lb_init: LBELL_K1_VARIANT=%s does not apply to these boxes\n", v);
+            delete ctx;
+            return LB_EINVAL;
+        }
+        ctx->k1_variant = std::atoi(v);
+    }
+    // an in-place variant starts in the layout of an even step, in one buffer
+    ctx->aa = K1_SHAPES[ctx->k1_variant].aa;
+    ctx->set_cur(ctx->aa ? 1 : 0);
     // box descriptors and tile table
     ctx->hbox.resize(nboxes);
     std::vector<int> tile_box(ctx->L.total_tiles), init(nboxes);
@@ -534,29 +574,12 @@ lb_status lb_init(const lb_config* cfg, int nboxes, const lb_box* boxes, void* d
                      ctx->stream));
     H(hipMemsetAsync(ctx->at<int>(ctx->L.flags), 0, sizeof(int) * 4, ctx->stream));
     H(launch_init(ctx->at<BoxDesc>(ctx->L.boxes), ctx->at<int>(ctx->L.tile_box), ctx->L.total_tiles, ctx->fbuf(0),
-                  ctx->fbuf(1), ctx->at<int>(ctx->L.box_init), kp, ctx->stream));
+                  ctx->aa ? nullptr : ctx->fbuf(1), ctx->at<int>(ctx->L.box_init), kp, ctx->stream));
     H(hipStreamSynchronize(ctx->stream));
     if (he != hipSuccess) {
         std::fprintf(stderr, "lb_init: %s\n", hipGetErrorString(he));
         delete ctx;
         return LB_EDEVICE;
-    }
-    // collide-stream variant: the row-wave kernel needs a single box whose x
-    // edge is 64, 128 or 256 sites
-    if (nboxes == 1 && cfg->lattice == 19 && (boxes[0].nx == 64 || boxes[0].nx == 128 || boxes[0].nx == 256)) {
-        ctx->rows_k = boxes[0].nx / 64;
-        ctx->k1_variant = 1;
-    }
-    if (const char* v = std::getenv("LBELL_OVERLAP")) ctx->overlap = std::atoi(v) != 0;
-    if (const char* v = std::getenv("LBELL_FUSED")) ctx->fused = std::atoi(v) != 0;
-    if (const char* v = std::getenv("LBELL_BAND")) ctx->use_band = std::atoi(v) != 0;
-    if (const char* v = std::getenv("LBELL_K1_VARIANT")) {
-        if (!k1_applicable(ctx, std::atoi(v))) {
-            std::fprintf(stderr, "lb_init: LBELL_K1_VARIANT=%s does not apply to these boxes\n", v);
-            delete ctx;
-            return LB_EINVAL;
-        }
-        ctx->k1_variant = std::atoi(v);
     }
     {
         int dev = 0, ncu = 0;
@@ -581,11 +604,6 @@ lb_status lb_init(const lb_config* cfg, int nboxes, const lb_box* boxes, void* d
             lb_destroy(ctx);
             return LB_EDEVICE;
         }
-    }
-    if (K1_SHAPES[ctx->k1_variant].aa && switch_layout(ctx, true) != LB_OK) {
-        std::fprintf(stderr, "lb_init: %s\n", ctx->err.c_str());
-        lb_destroy(ctx);
-        return LB_EDEVICE;
     }
     *out = ctx;
     return LB_OK;

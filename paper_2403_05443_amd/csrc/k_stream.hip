@@ -629,7 +629,9 @@ __global__ __launch_bounds__(TILE) void k_init(const BoxDesc* __restrict__ boxes
 }
 
 // Pre-collision density / velocity of fluid sites of one box, for a chunk of
-// sites [s0, s0 + count): out[4*k] = rho, out[4*k+1..3] = u (zeros elsewhere).
+// sites [s0, s0 + count): out[k] = rho, out[count + 3 k ..] = u (zeros
+// elsewhere), the layout of the caller's arrays, so that they are copied as they
+// are.
 template <int ST, int Q>
 __global__ __launch_bounds__(TILE) void k_fields(const BoxDesc* __restrict__ boxes, int bi,
                                                  const uint16_t* __restrict__ omap,
@@ -658,10 +660,11 @@ __global__ __launch_bounds__(TILE) void k_fields(const BoxDesc* __restrict__ box
         rho = kp.rho0 + d;
         for (int c = 0; c < 3; ++c) u[c] = j[c] / rho;
     }
-    out[4 * k] = rho;
-    out[4 * k + 1] = u[0];
-    out[4 * k + 2] = u[1];
-    out[4 * k + 3] = u[2];
+    out[k] = rho;
+    double* ou = out + count + 3 * (long long)k;
+    ou[0] = u[0];
+    ou[1] = u[1];
+    ou[2] = u[2];
 }
 
 __device__ __forceinline__ double wave_sum_d(double v) {

@@ -471,6 +471,15 @@ struct SolveShm {
     double rhs[6];    // right-hand side, kept for the predictor-corrector
 };
 
+// The box of a particle.  ONE: the context's only particle, whose box comes with
+// the launch (the counter-force is read from boxes, since it can change
+// between the replays of a captured graph).
+template <bool ONE>
+__device__ __forceinline__ const BoxDesc& box_of(const LaunchPart& a, int box) {
+    if constexpr (ONE) return a.one;
+    else return a.boxes[box];
+}
+
 // The links of one thread (l = tid + k PBLOCK, k < KREG): codes and stored
 // post-collision populations, held in registers from the force reduction to
 // the bounce-back.
@@ -485,8 +494,11 @@ struct LinkRegs {
 // code loads go out together, then the population loads, and those stay in
 // flight across the LDS write and the barrier.  A lane without a link reads
 // element 0 of the box (always valid) and never uses it, so no load sits in
-// a branch, where its use, and a wait for it, would follow at once.
-template <int ST, int Q>
+// a branch, where its use, and a wait for it, would follow at once.  ONE: the
+// box and the links' place are launch arguments, so the codes are loaded beside
+// the record (every particle's share of the pool holds KREG PBLOCK codes) and
+// two round trips fall out of the chain.
+template <int ST, int Q, bool ONE>
 __device__ __forceinline__ void load_particle(const LaunchPart& a, int p, PartDev* Pl,
                                               LinkRegs<typename Store<ST>::T>& lr) {
     using T = typename Store<ST>::T;
@@ -496,15 +508,19 @@ __device__ __forceinline__ void load_particle(const LaunchPart& a, int p, PartDe
     const int tid = threadIdx.x;
     const unsigned long long sv = tid < NW ? reinterpret_cast<const unsigned long long*>(Pg)[tid] : 0ull;
     const int nl = Pg->nlinks;
-    const BoxDesc& B = a.boxes[Pg->box];
-    const uint32_t* L = a.links + Pg->lbase;
+    const BoxDesc& B = box_of<ONE>(a, ONE ? 0 : Pg->box);
+    const uint32_t* L = a.links + (ONE ? a.one_lbase : Pg->lbase);
     const T* f = (const T*)a.f + B.foff;
     const int cv = a.kp.conv;
     const double rnx = 1.0 / B.nx, rny = 1.0 / B.ny;
 #pragma unroll
     for (int k = 0; k < KREG; ++k) {
         const int l = tid + k * PBLOCK;
-        lr.code[k] = l < nl ? L[l] : 0u;
+        lr.code[k] = ONE || l < nl ? L[l] : 0u;
+    }
+    if constexpr (ONE) {
+#pragma unroll
+        for (int k = 0; k < KREG; ++k) lr.code[k] = tid + k * PBLOCK < nl ? lr.code[k] : 0u;
     }
 #pragma unroll
     for (int k = 0; k < KREG; ++k)
@@ -536,7 +552,7 @@ __device__ __forceinline__ void accept_solution(const LaunchPart& a, const PartD
 
 // Steps 3-7 for particle p whose record is staged in LDS (P).  The new state
 // goes to global memory; with keep_lds the LDS copy is updated as well.
-template <int ST, int Q>
+template <int ST, int Q, bool ONE>
 __device__ __forceinline__ void solve_phase(const LaunchPart& a, int p, PartDev& P, SolveShm& sh,
                                             const LinkRegs<typename Store<ST>::T>& lr, bool keep_lds) {
     using S = Store<ST>;
@@ -544,7 +560,9 @@ __device__ __forceinline__ void solve_phase(const LaunchPart& a, int p, PartDev&
     double (*red)[PWAVES] = sh.red;
     double* bc = sh.bc;
     PartDev* Pg = a.parts + p;
-    const BoxDesc& B = a.boxes[P.box];
+    const BoxDesc& B = box_of<ONE>(a, P.box);
+    // -fext / (n - n_wall) with the counter-force, else 0 (loaded ahead of its use)
+    const double gcf3[3] = {a.boxes[P.box].gcf[0], a.boxes[P.box].gcf[1], a.boxes[P.box].gcf[2]};
     T* f = (T*)a.f + B.foff;
     const long long st = B.stride;
     const int nx = B.nx, ny = B.ny, nz = B.nz, tid = threadIdx.x;
@@ -701,7 +719,7 @@ __device__ __forceinline__ void solve_phase(const LaunchPart& a, int p, PartDev&
         double rhs[6];
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
-            const double gcf = B.gcf[i];  // -fext / (n - n_wall) with the counter-force, else 0
+            const double gcf = gcf3[i];
             rhs[i] = M * U0[i] + acc[i] + P.Fext[i] + P.n_solid * gcf + P.Pp[i];
             rhs[3 + i] = sh.IW[i] + acc[3 + i] + P.Text[i] + P.Lp[i];
         }
@@ -1886,13 +1904,13 @@ __device__ __forceinline__ void link_pass(const LaunchPart& a, int p, const Part
 // other work-groups.  stores_done: the bounce-back stores of the step are
 // complete (a kernel boundary lies between); otherwise the claims wait for
 // them first.
-template <int ST, int Q>
+template <int ST, int Q, bool ONE>
 __device__ __forceinline__ void remap_phase(const LaunchPart& a, int p, PartDev& P, RemapShm& sh, uint32_t* smem,
                                             bool stores_done) {
     uint32_t* bits = smem;
     uint32_t* stage = smem + a.lds_words;
     uint32_t* cand = stage;  // the candidate bits are consumed before the links are staged
-    const BoxDesc& B = a.boxes[P.box];
+    const BoxDesc& B = box_of<ONE>(a, P.box);
     Win w;
     if (!window_of(a, P, B, w)) return;
     const int mode = a.mode;
@@ -1935,13 +1953,13 @@ __global__ __launch_bounds__(PBLOCK) void k_particle_remap(LaunchPart a) {
     __shared__ RemapShm sh;
     const int p = a.first + (int)blockIdx.x;
     stage_particle(a.parts + p, &P);
-    remap_phase<ST, Q>(a, p, P, sh, smem, true);
+    remap_phase<ST, Q, false>(a, p, P, sh, smem, true);
 }
 
 // Steps 3-9 in one work-group, for boxes that hold one particle: the record
 // is staged once, and the remap reads the bounce-back writes of its own
 // work-group (no other particle writes this box).
-template <int ST, int Q>
+template <int ST, int Q, bool ONE>
 __global__ __launch_bounds__(PBLOCK) void k_particle_step(LaunchPart a) {
     extern __shared__ uint32_t smem[];
     __shared__ PartDev P;
@@ -1951,12 +1969,12 @@ __global__ __launch_bounds__(PBLOCK) void k_particle_step(LaunchPart a) {
     } sh;
     const int p = a.first + (int)blockIdx.x;
     LinkRegs<typename Store<ST>::T> lr;
-    load_particle<ST, Q>(a, p, &P, lr);
-    solve_phase<ST, Q>(a, p, P, sh.s, lr, true);
+    load_particle<ST, Q, ONE>(a, p, &P, lr);
+    solve_phase<ST, Q, ONE>(a, p, P, sh.s, lr, true);
     // the new state in LDS before the remap; the bounce-back stores may still
     // be in flight (the remap waits for them only before its claims)
     lds_barrier();
-    remap_phase<ST, Q>(a, p, P, sh.r, smem, false);
+    remap_phase<ST, Q, ONE>(a, p, P, sh.r, smem, false);
 }
 
 // Boxes with several particles take three kernels per step, so that every
@@ -1976,8 +1994,8 @@ __global__ __launch_bounds__(PBLOCK) void k_particle_solve_map(LaunchPart a) {
     } sh;
     const int p = a.first + (int)blockIdx.x;
     LinkRegs<typename Store<ST>::T> lr;
-    load_particle<ST, Q>(a, p, &P, lr);
-    solve_phase<ST, Q>(a, p, P, sh.s, lr, true);
+    load_particle<ST, Q, false>(a, p, &P, lr);
+    solve_phase<ST, Q, false>(a, p, P, sh.s, lr, true);
     lds_barrier();
     PartDev* Pg = a.parts + p;
     const BoxDesc& B = a.boxes[P.box];
@@ -2118,14 +2136,22 @@ static hipError_t remap_one(const LaunchPart& a, hipStream_t st) {
     return hipGetLastError();
 }
 
+template <int ST, int Q>
+static void step_one(const LaunchPart& a, hipStream_t st) {
+    const size_t lds = particle_remap_lds_bytes(a.lds_words);
+    if (a.one_part)
+        hipLaunchKernelGGL((k_particle_step<ST, Q, true>), dim3(a.count), dim3(PBLOCK), lds, st, a);
+    else
+        hipLaunchKernelGGL((k_particle_step<ST, Q, false>), dim3(a.count), dim3(PBLOCK), lds, st, a);
+}
+
 template <int Q>
 static hipError_t step_q(const LaunchPart& a, hipStream_t st) {
-    const size_t lds = particle_remap_lds_bytes(a.lds_words);
     switch (a.kp.storage) {
-        case ST_F64: hipLaunchKernelGGL((k_particle_step<ST_F64, Q>), dim3(a.count), dim3(PBLOCK), lds, st, a); break;
-        case ST_F32: hipLaunchKernelGGL((k_particle_step<ST_F32, Q>), dim3(a.count), dim3(PBLOCK), lds, st, a); break;
-        case ST_F16: hipLaunchKernelGGL((k_particle_step<ST_F16, Q>), dim3(a.count), dim3(PBLOCK), lds, st, a); break;
-        default: hipLaunchKernelGGL((k_particle_step<ST_BF16, Q>), dim3(a.count), dim3(PBLOCK), lds, st, a); break;
+        case ST_F64: step_one<ST_F64, Q>(a, st); break;
+        case ST_F32: step_one<ST_F32, Q>(a, st); break;
+        case ST_F16: step_one<ST_F16, Q>(a, st); break;
+        default: step_one<ST_BF16, Q>(a, st); break;
     }
     return hipGetLastError();
 }

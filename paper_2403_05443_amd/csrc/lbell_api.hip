@@ -348,6 +348,11 @@ LaunchPart part_launch(lb_ctx* ctx, int first, int count, int mode) {
     a.force_box = -1;
     a.band = ctx->at<uint32_t>(ctx->L.band);
     a.use_band = ctx->use_band ? 1 : 0;
+    a.one_part = ctx->np == 1 ? 1 : 0;
+    if (a.one_part) {
+        a.one = ctx->hbox[ctx->hpart[0].box];
+        a.one_lbase = 0;  // the first particle's links lead the pool
+    }
     return a;
 }
 
@@ -739,6 +744,8 @@ namespace {
 LaunchCS collide_args(lb_ctx* ctx, int variant) {
     LaunchCS cs{};
     cs.boxes = ctx->at<BoxDesc>(ctx->L.boxes);
+    cs.one_box = ctx->boxes.size() == 1;
+    if (cs.one_box) cs.one = ctx->hbox[0];
     cs.rt = ctx->at<BoxRT>(ctx->L.rt);
     cs.tile_box = ctx->at<int>(ctx->L.tile_box);
     cs.ntiles = ctx->L.total_tiles;

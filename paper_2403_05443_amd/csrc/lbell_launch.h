@@ -6,6 +6,8 @@ namespace lbd {
 
 struct LaunchCS {
     const BoxDesc* boxes;
+    BoxDesc one;            // one_box: the context's only box (its counter-force is read from boxes)
+    bool one_box;
     const BoxRT* rt;
     const int* tile_box;
     int ntiles;
@@ -62,6 +64,9 @@ hipError_t launch_poke(const BoxDesc* boxes, int bi, void* f, int s, int dir, do
 
 struct LaunchPart {
     const BoxDesc* boxes;
+    BoxDesc one;            // one_part: the only particle's box (its counter-force is read from boxes),
+    long long one_lbase;    // and the particle's first link in the pool
+    int one_part;
     BoxRT* rt;
     PartDev* parts;
     uint32_t* links;

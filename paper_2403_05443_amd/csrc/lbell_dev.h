@@ -255,6 +255,21 @@ namespace lbd {
 constexpr int ST_F64 = 0, ST_F32 = 1, ST_F16 = 2, ST_BF16 = 3;
 
 // Stored value <-> deviation f_i - w_i rho0 in the collision precision R.
+// Nearest half (ties to even) of a double.  Rounded first to odd at float's 24
+// bits (the 29 below them folded into the last one kept), which the second
+// rounding to half's 11 cannot tell from the exact value.  gfx950 has no
+// instruction for it, and the compiler's own sequence is about 35 integer
+// operations: the start field's store of 19 populations was 868 vector
+// instructions a node and bound by them (64 boxes, 7.7 M nodes: 207 us, now
+// 123).  Without contraction, which would join the two conversions again.
+__device__ __forceinline__ _Float16 f64_to_f16(double v) {
+#pragma clang fp contract(off)
+    const uint32_t lo = (uint32_t)__double2loint(v), keep = lo & 0xE0000000u;
+    const uint32_t odd = min(lo & 0x1FFFFFFFu, 1u) << 29;
+    const float f = (float)__hiloint2double(__double2hiint(v), (int)(keep | odd));
+    return (_Float16)f;
+}
+
 template <int ST> struct Store;
 template <> struct Store<ST_F64> {
     using T = double;
@@ -298,7 +313,7 @@ template <> struct Store<ST_F16> {
     }
     static __device__ __forceinline__ double ld64(const T* p, double inv) { return (double)(float)*p * inv; }
     static __device__ __forceinline__ double cv64(T v, double inv) { return (double)(float)v * inv; }
-    static __device__ __forceinline__ void st64(T* p, double v, double s) { *p = (_Float16)(float)(v * s); }
+    static __device__ __forceinline__ void st64(T* p, double v, double s) { *p = f64_to_f16(v * s); }
 };
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 __device__ __forceinline__ uint16_t f32_to_bf16(float f) {

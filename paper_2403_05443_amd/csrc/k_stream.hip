@@ -652,7 +652,8 @@ __global__ __launch_bounds__(TILE) void k_fields(const BoxDesc* __restrict__ box
     double rho = 0, u[3] = {0, 0, 0};
     if (omap[B.ooff + s] == 0) {
         const int nx = B.nx, ny = B.ny;
-        const int x = s % nx, t = s / nx, y = t % ny, z = t / ny;
+        int x, y;
+        const int z = div_magic(div_magic(s, nx, B.mnx, B.lnx, x), ny, B.mny, B.lny, y);
         R f[Q];
         Pull<ST, Q>::pull_cv(kp.conv, B, fin + B.foff, s, x, y, z, (R)kp.inv_scale, (R)kp.rho0, B.walls != 0, f);
         double d = 0, j[3] = {0, 0, 0};
@@ -690,7 +691,8 @@ __global__ __launch_bounds__(TILE) void k_moments(const BoxDesc* __restrict__ bo
     double v[6] = {0, 0, 0, 0, 0, 0};
     if (s < B.n && omap[B.ooff + s] == 0) {
         const int nx = B.nx, ny = B.ny;
-        const int x = s % nx, t = s / nx, y = t % ny, z = t / ny;
+        int x, y;
+        const int z = div_magic(div_magic(s, nx, B.mnx, B.lnx, x), ny, B.mny, B.lny, y);
         R f[Q];
         Pull<ST, Q>::pull_cv(kp.conv, B, fin + B.foff, s, x, y, z, (R)kp.inv_scale, (R)kp.rho0, B.walls != 0, f);
         v[0] = 1.0;
@@ -740,7 +742,8 @@ __global__ __launch_bounds__(TILE) void k_box_energy(const BoxDesc* __restrict__
     double e = 0.0;
     if (s < B.n && omap[B.ooff + s] == 0) {
         const int nx = B.nx, ny = B.ny;
-        const int x = s % nx, t = s / nx, y = t % ny, z = t / ny;
+        int x, y;
+        const int z = div_magic(div_magic(s, nx, B.mnx, B.lnx, x), ny, B.mny, B.lny, y);
         R f[Q];
         Pull<ST, Q>::pull_cv(kp.conv, B, fin + B.foff, s, x, y, z, (R)kp.inv_scale, (R)kp.rho0, B.walls != 0, f);
         double j[3] = {0, 0, 0};

@@ -340,6 +340,15 @@ __global__ void k_stokes_prep(const PartDev* __restrict__ parts, int np, double 
     if (use) flow_const(parts[p], mu, fc[p]);
 }
 
+// x^(-1/2) of a normal x > 0: the instruction's estimate and one third-order
+// step, y (1 + e (1/2 + 3 e / 8)), e = 1 - x y^2, without the library's
+// selects for zero and infinity (R2 is a squared distance outside the body).
+__device__ __forceinline__ double inv_sqrt(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
 // The eight integrals of particle_flow, a point at a time.
 struct LineSums {
     double A, B, Bz, C, Cz, D, E, pr;
@@ -348,7 +357,7 @@ template <bool TORQUE>
 __device__ __forceinline__ void line_point(const FlowConst& K, double n2, double Sn, double nm, double zeta, double g,
                                            double wq, LineSums& I) {
     const double R2 = n2 + zeta * zeta;
-    const double iR = rsqrt(R2), iR2 = iR * iR, iR3 = iR * iR2;
+    const double iR = inv_sqrt(R2), iR2 = iR * iR, iR3 = iR * iR2;
     const double Sr = Sn + K.Sp * zeta, cS3 = K.bfac * g * iR2;  // cS3 / R: the dipoles' weight over R^3
     double B = Sr * iR3 * (1.0 + 3.0 * cS3), pr = Sr * iR3;
     I.A += wq * (iR * (1.0 - cS3));
@@ -371,13 +380,15 @@ template <bool TORQUE>
 __device__ __forceinline__ void line_sums(const FlowConst& K, double z, double n2, double Sn, double nm, LineSums& I) {
     const double f = K.f;
     const double x0 = fmin(fmax(z, -f), f), zx = z - x0;
-    const double delta = sqrt(n2 + zx * zx);  // > 0: the segment lies inside the body
-    const double q = delta * K.if_;
+    const double d2 = n2 + zx * zx;  // delta^2 > 0: the segment lies inside the body
+    const double q2 = d2 * (K.if_ * K.if_);
+    // (delta / f)^2 below the square of a line
+    auto below = [&](double line) { return q2 < line * line; };
     // the rule is the wave's: the one its nearest node on this side of 0.8 f
     // needs (so the table is read with scalar loads and no lane waits for a
     // longer rule than its own row of nodes)
-    if (q >= 0.8) {
-        const bool b1 = __any(q < 1.15), b2 = __any(q < 1.95), b3 = __any(q < 3.2), b4 = __any(q < 9.0);
+    if (!below(0.8)) {
+        const bool b1 = __any(below(1.15)), b2 = __any(below(1.95)), b3 = __any(below(3.2)), b4 = __any(below(9.0));
         const int row = b1 ? GL32 : (b2 ? GL24 : (b3 ? GL16 : (b4 ? GL12 : GL8)));
         const int half = b1 ? 16 : (b2 ? 12 : (b3 ? 8 : (b4 ? 6 : 4)));
 #pragma unroll 2
@@ -388,9 +399,9 @@ __device__ __forceinline__ void line_sums(const FlowConst& K, double z, double n
         }
         return;
     }
-    const bool near = __any(q < 0.5);
+    const bool near = __any(below(0.5));
     const int row = near ? GL24 : GL16, half = near ? 12 : 8;
-    const double idel = 1.0 / delta;
+    const double idel = inv_sqrt(d2), delta = d2 * idel;
     for (int side = 0; side < 2; ++side) {
         const double sgn = side ? 1.0 : -1.0, len = side ? f - x0 : x0 + f;
         if (len <= 0.0) continue;
@@ -454,10 +465,13 @@ __device__ __forceinline__ void particle_flow(const FlowConst& K, const double d
 // over each box's loaded particles of particle_flow), node-major into uf at
 // UF * (ooff + site - base).  A work-group per tile; the box's loaded particles
 // are listed in index order, TILE at a time, in LDS.
-// Bound by FP64 arithmetic; four waves to a SIMD at the price of 30 spilled
-// values beat two without (440 against 565 us on 64 boxes, 7.7 M nodes;
-// 1507 us with the constants per node, two-sided rules everywhere and the
-// vector terms inside the quadrature).
+// Bound by FP64 arithmetic (84 % of the issue slots; 28 operations a point);
+// four waves to a SIMD at the price of 29 spilled values beat two without, and
+// three are no better.  64 boxes, 7.7 M nodes: 412 us (461 with the library's
+// rsqrt, a square root for the rule and divisions for the node's place; 1507
+// with the constants per node, two-sided rules everywhere and the vector terms
+// inside the quadrature).  Waves of 4 x 4 x 4 nodes in place of rows would need
+// 5 to 10 % fewer points.
 __global__ __launch_bounds__(TILE, 4) void k_stokes_free(const BoxDesc* __restrict__ boxes,
                                                       const int* __restrict__ tile_box,
                                                       const FlowConst* __restrict__ fc,
@@ -470,7 +484,8 @@ __global__ __launch_bounds__(TILE, 4) void k_stokes_free(const BoxDesc* __restri
     if (only_box >= 0 && bi != only_box) return;  // uniform over the block
     const BoxDesc& B = boxes[bi];
     const int s = (tile - B.tile0) * TILE + tid;
-    const int x = s % B.nx, t = s / B.nx, y = t % B.ny, z = t / B.ny;
+    int x, y;
+    const int z = div_magic(div_magic(s, B.nx, B.mnx, B.lnx, x), B.ny, B.mny, B.lny, y);
     double u[UF] = {0.0, 0.0, 0.0, 0.0};
     for (int p0 = 0; p0 < np; p0 += TILE) {
         const int p = p0 + tid;
@@ -585,6 +600,27 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+// The wave's sums of eight values, value (lane >> 3) returned to each lane: the
+// lanes share out the values at the first three levels (10 exchanges; wave_sum
+// of each takes 48), the additions are wave_sum's.
+__device__ __forceinline__ double wave_sum8(const double (&v)[8], int lane) {
+    double a[4], b[2];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const bool up = lane & 32;
+        a[k] = (up ? v[k + 4] : v[k]) + __shfl_xor(up ? v[k] : v[k + 4], 32);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const bool up = lane & 16;
+        b[k] = (up ? a[k + 2] : a[k]) + __shfl_xor(up ? a[k] : a[k + 2], 16);
+    }
+    const bool up = lane & 8;
+    double w = (up ? b[1] : b[0]) + __shfl_xor(up ? b[0] : b[1], 8);
+    for (int off = 4; off > 0; off >>= 1) w += __shfl_xor(w, off);
+    return w;
+}
+
 // Discrete Fourier sums S_n = sum_x (u, p)_free(x) exp(-i k_n . x), |n_i| <= WK,
 // over the planes z = slab, slab + nslab, ... of a box, an axis at a time (the
 // field is real, so n_y >= 0 suffices: the others are conjugates).  Along y:
@@ -594,13 +630,17 @@ __device__ __forceinline__ double wave_sum(double v) {
 // an output.  Along z: the plane's outputs times exp(-i kz z) for the five n_z,
 // kept in registers over the slab's planes.  The field is read once, about 60
 // operations a node; a work-group per (n_y, n_z) pair read it 25 times over and
-// spent 400 a node in all.  One 96^3 box 1500 -> 25 us (25 -> 96 work-groups), 64
-// boxes of edges 32-64 (7.7 M nodes) 1108 -> 168 us.
+// spent 400 a node in all.  Bound by the chain of a plane's four phases; three
+// work-groups fit a compute unit (LDS, registers: a fourth would need less of
+// both).  One 96^3 box 1500 -> 22 us (25 -> 96 work-groups), 64 boxes of edges
+// 32-64 (7.7 M nodes) 1108 -> 84 us (165 with a serial x sum over one bank and
+// slabs twice and four times the size, the last of which ran on few compute
+// units).
 constexpr int YT = 128;  // rows of the phase table held in LDS at a time
 __global__ __launch_bounds__(256) void k_stokes_modes(const BoxDesc* __restrict__ boxes,
                                                       const double* __restrict__ uf, long long base, int only_box,
                                                       int box_slabs, double* __restrict__ S) {
-    __shared__ double Bs[(2 * WK + 1) * UF][256];
+    __shared__ double Bs[(2 * WK + 1) * UF][257];  // odd rows: the x sum reads a column of them
     __shared__ double ty[YT][4], tx[256][4];  // (cos, sin) of n = 1 and of n = 2
     const int bi = blockIdx.x / box_slabs, slab = blockIdx.x % box_slabs, tid = threadIdx.x;
     if (only_box >= 0 && bi != only_box) return;  // uniform over the block
@@ -667,6 +707,7 @@ __global__ __launch_bounds__(256) void k_stokes_modes(const BoxDesc* __restrict_
                 for (int i = tid; i < (2 * WK + 1) * UF * cw; i += 256) {
                     const int j = i / cw, xx = i % cw;
                     double v = Bs[j][xx];
+#pragma unroll 4
                     for (int h = 1; h < ng; ++h) v += Bs[j][h * cw + xx];
                     Bs[j][xx] = v;
                 }
@@ -675,11 +716,12 @@ __global__ __launch_bounds__(256) void k_stokes_modes(const BoxDesc* __restrict_
             if (seg < NSEG) {
                 const double* br = Bs[ok * (2 * WK + 1) + (oy ? 2 * oy - 1 : 0)];
                 const double* bm = Bs[ok * (2 * WK + 1) + (oy ? 2 * oy : 0)];
-                const int an = ox < 0 ? -ox : ox;
+                const double* tn = &tx[0][ox ? 2 * abs(ox) - 2 : 0];
+                // n_x = 0: (1, 0) for (c, sn); n_y = 0: no imaginary sum
+                const double cf = ox ? 1.0 : 0.0, sf = ox < 0 ? -1.0 : cf, mf = oy ? 1.0 : 0.0;
+#pragma unroll 4
                 for (int xx = seg; xx < cw; xx += NSEG) {
-                    const double c = an ? tx[xx][2 * an - 2] : 1.0;
-                    const double sn = an ? (ox < 0 ? -tx[xx][2 * an - 1] : tx[xx][2 * an - 1]) : 0.0;
-                    const double r = br[xx], m = oy ? bm[xx] : 0.0;
+                    const double c = cf * tn[4 * xx] + (1.0 - cf), sn = sf * tn[4 * xx + 1], r = br[xx], m = mf * bm[xx];
                     pr += r * c + m * sn;  // (r + i m) (c - i sn)
                     pi += m * c - r * sn;
                 }
@@ -823,8 +865,10 @@ __global__ __launch_bounds__(128) void k_stokes_coef(const BoxDesc* __restrict__
 // The periodic correction added to the staged field at every fluid node, in
 // place, and the tile's partial sums over its fluid nodes: of u (3), of p u
 // (3), of p and the count.  Writing the corrected field back costs 32 bytes a
-// node and spares k_stokes_write the correction (64 boxes: 411 -> 192 us here,
-// 463 -> 207 us there).
+// node and spares k_stokes_write the correction.  Bound by the rows' coefficients
+// and the sums beside 66 bytes a node: 64 boxes, 7.7 M nodes, 143 us (82 at the
+// copy rate; 411 with the correction unfactored, 197 with the node loaded after
+// the coefficients and a full exchange for each of the eight sums).
 __global__ __launch_bounds__(TILE) void k_stokes_sum(const BoxDesc* __restrict__ boxes,
                                                      const int* __restrict__ tile_box,
                                                      const uint16_t* __restrict__ omap,
@@ -841,10 +885,17 @@ __global__ __launch_bounds__(TILE) void k_stokes_sum(const BoxDesc* __restrict__
     double v[NPART] = {0, 0, 0, 0, 0, 0, 0, 0};
     const bool started = only_box < 0 || bi == only_box;  // uniform over the block
     int row0 = 0;
+    // the node's loads are under way while the rows' coefficients are formed
+    double2* o = reinterpret_cast<double2*>(uf + UF * (B.ooff + s - base));
+    double2 q0 = {0.0, 0.0}, q1 = {0.0, 0.0};
+    uint16_t owner = 0xFFFF;
+    if (started && s < B.n) {
+        owner = omap[B.ooff + s];
+        q0 = o[0];
+        q1 = o[1];
+    }
     if (started) row0 = row_coefs(B, coef + (long long)bi * WM * MC, (tile - B.tile0) * TILE, Z, R);
-    if (started && s < B.n && omap[B.ooff + s] == 0) {
-        double2* o = reinterpret_cast<double2*>(uf + UF * (B.ooff + s - base));
-        const double2 q0 = o[0], q1 = o[1];
+    if (owner == 0) {
         double u[UF] = {q0.x, q0.y, q1.x, q1.y};
         int x;
         const int row = div_magic(s, B.nx, B.mnx, B.lnx, x);
@@ -867,11 +918,8 @@ __global__ __launch_bounds__(TILE) void k_stokes_sum(const BoxDesc* __restrict__
         v[6] = u[3];
         v[7] = 1.0;
     }
-#pragma unroll
-    for (int k = 0; k < NPART; ++k) {
-        const double w = wave_sum(v[k]);
-        if ((tid & 63) == 0) red[tid >> 6][k] = w;
-    }
+    const double w8 = wave_sum8(v, tid & 63);
+    if ((tid & 7) == 0) red[tid >> 6][(tid >> 3) & 7] = w8;
     __syncthreads();
     if (tid < NPART) {
         double w = 0.0;
@@ -914,9 +962,10 @@ __global__ __launch_bounds__(256) void k_stokes_mean(const BoxDesc* __restrict__
     ubar[4 * b + 3] = pbar;
 }
 
-// Bound by memory (a staged node read, Q populations written); the storage
-// convention is a template parameter so that a slot costs an addition, and the
-// two directions of a pair share their products.
+// Bound by memory (a staged node read, Q populations written: in FP16 70 bytes
+// a node, 64 boxes 123 us, 86 at the copy rate, 463 with the correction here
+// too); the storage convention is a template parameter so that a slot costs an
+// addition, and the two directions of a pair share their products.
 template <int ST, int Q, int CV>
 __global__ __launch_bounds__(TILE) void k_stokes_write(const BoxDesc* __restrict__ boxes,
                                                        const int* __restrict__ tile_box,
@@ -933,6 +982,9 @@ __global__ __launch_bounds__(TILE) void k_stokes_write(const BoxDesc* __restrict
     const BoxDesc& B = boxes[bi];
     const int s = (tile - B.tile0) * TILE + (int)threadIdx.x;
     if (s >= B.n) return;
+    // the staged node comes with its owner, not after it
+    const double2* o = reinterpret_cast<const double2*>(uf + UF * (B.ooff + s - base));
+    const double2 q0 = o[0], q1 = o[1];
     const uint16_t owner = omap[B.ooff + s];
     if (owner == 0xFFFF) return;
     const int nx = B.nx, ny = B.ny, nz = B.nz;
@@ -941,8 +993,6 @@ __global__ __launch_bounds__(TILE) void k_stokes_write(const BoxDesc* __restrict
     const double rho0 = kp.rho0;
     double rho = rho0, u[3];
     if (owner == 0) {
-        const double2* o = reinterpret_cast<const double2*>(uf + UF * (B.ooff + s - base));
-        const double2 q0 = o[0], q1 = o[1];
         u[0] = q0.x - ubar[4 * bi];
         u[1] = q0.y - ubar[4 * bi + 1];
         u[2] = q1.x - ubar[4 * bi + 2];
@@ -1151,13 +1201,15 @@ hipError_t launch_warm_targets(const PartDev* parts, int np, const double* s, do
     return hipGetLastError();
 }
 
-// Planes of a box are dealt to slabs of about 8192 nodes (1 to 512 of them, no
-// more than planes): enough work-groups for one large box, a few sums to add
-// for a small one.  A function of the box alone, so a box's sums do not depend on
+// Planes of a box are dealt to slabs of about 2048 nodes (1 to 512 of them, no
+// more than planes): enough work-groups for one large box, and for many small
+// ones several rounds of them, so that the last is not a large part of the time (64
+// boxes, 7.7 M nodes: 165 us with 8192 nodes, 111 with 4096, 84 with
+// 2048; a slab's sums are 4.8 KB).  A function of the box alone, so a box's sums do not depend on
 // what else is started.
 int stokes_slabs(int nx, int ny, int nz) {
     const long long n = (long long)nx * ny * nz;
-    return (int)std::max<long long>(1, std::min<long long>(std::min<long long>(nz, 512), n / 8192));
+    return (int)std::max<long long>(1, std::min<long long>(std::min<long long>(nz, 512), n / 2048));
 }
 
 void stokes_tile(int nx, int ny, int& rows, int& planes) {

@@ -1657,6 +1657,30 @@ __device__ __forceinline__ uint32_t shell_word(const uint32_t* bits, int nwords,
     return any & ~bits[wi];
 }
 
+// The directions in which window node i has a solid neighbour: three bits of
+// each of the nine rows around it.  For the windows of shell_word, whose
+// outermost layers hold no solid node; all loads go out together (18 tests, each
+// with its own wait on LDS, took 10000 cycles of a rebuild's 48000 on 800
+// squirmers).
+template <int Q>
+__device__ __forceinline__ uint32_t link_mask(const uint32_t* bits, int nwords, int i, int wx, int wxy) {
+    uint32_t row[9];
+    auto word = [&](int k) {
+        const uint32_t v = bits[min((unsigned)k, (unsigned)(nwords - 1))];
+        return (unsigned)k < (unsigned)nwords ? v : 0u;
+    };
+#pragma unroll
+    for (int d = 0; d < 9; ++d) {
+        // bit 0 of row[d] is node (-1, dy, dz) from i
+        const int n0 = i + (d % 3 - 1) * wx + (d / 3 - 1) * wxy - 1, k = n0 >> 5;
+        row[d] = __builtin_amdgcn_alignbit(word(k + 1), word(k), n0 & 31);
+    }
+    uint32_t m = 0;
+#pragma unroll
+    for (int b = 1; b < Q; ++b) m |= ((row[3 * (cz(b) + 1) + cy(b) + 1] >> (cx(b) + 1)) & 1u) << b;
+    return m;
+}
+
 // Pass 2: the boundary links (fluid x, x + c_b solid of this particle; bits
 // holds this particle's nodes over the window), staged in LDS and written in
 // (window index, direction) order, and their moments, from which zeta of
@@ -1727,9 +1751,26 @@ __device__ __forceinline__ void link_pass(const LaunchPart& a, int p, const Part
         nc += t;
     }
 
+    static_assert(KLINK * PBLOCK + 2 * PBLOCK <= STAGE, "a word and its place per thread lie behind the list");
+    uint32_t* wmask = stage + KLINK * PBLOCK;
+    uint32_t* wplace = wmask + PBLOCK;
+    int ni_[KLINK];
+    uint32_t lmv[KLINK];
     for (int r0 = 0; r0 < nc; r0 += KLINK * PBLOCK) {
         const int r1 = min(nc, r0 + KLINK * PBLOCK);
-        if (base < r1 && base + cnt > r0) {
+        if (per == 1) {
+            // a window of one word a thread at most: the words are shared out
+            // again, 64 nodes to a wave at a time and a lane to a node (a word's
+            // thread would write up to 32 places one after another)
+            wmask[tid] = first;
+            wplace[tid] = (uint32_t)base;
+            __syncthreads();
+            for (int c = wv; 2 * c < nwords; c += PWAVES) {
+                const unsigned long long m = wmask[2 * c] | (unsigned long long)wmask[2 * c + 1] << 32;
+                const int o = (int)wplace[2 * c] + __popcll(m & ((1ull << lane) - 1ull));
+                if ((m >> lane) & 1ull && o >= r0 && o < r1) stage[o - r0] = (uint32_t)(64 * c + lane);
+            }
+        } else if (base < r1 && base + cnt > r0) {
             int o = base;
             for (int j = 0; j < per; ++j) {
                 const int wi = tid * per + j;
@@ -1745,14 +1786,14 @@ __device__ __forceinline__ void link_pass(const LaunchPart& a, int p, const Part
         __syncthreads();
         // link masks of the listed nodes: bit b set when the node is fluid and
         // its neighbour along c_b is solid here
-        int ni_[KLINK], wi_[KLINK][3], sv[KLINK], offv[KLINK];
-        uint32_t lmv[KLINK];
+        int wi_[KLINK][3], sv[KLINK], offv[KLINK];
         uint16_t own[KLINK];
 #pragma unroll
         for (int c = 0; c < KLINK; ++c) {
             const int k = r0 + c * PBLOCK + tid;
             own[c] = 1;  // not fluid
             sv[c] = 0;
+            ni_[c] = 0;
             if (k < r1) {
                 const int i = (int)stage[k - r0];
                 ni_[c] = i;
@@ -1765,7 +1806,10 @@ __device__ __forceinline__ void link_pass(const LaunchPart& a, int p, const Part
 #pragma unroll
         for (int c = 0; c < KLINK; ++c) {
             uint32_t lm = 0;
-            if (own[c] == 0) {
+            if (!wraps) {
+                lm = link_mask<Q>(bits, nwords, ni_[c], wx1, wxy);  // beside the node-map load
+                lm = own[c] == 0 ? lm : 0u;
+            } else if (own[c] == 0) {
 #pragma unroll
                 for (int b = 1; b < Q; ++b) {
                     int nwx = wi_[c][0] + cx(b), nwy = wi_[c][1] + cy(b), nwz = wi_[c][2] + cz(b);
@@ -1828,6 +1872,7 @@ __device__ __forceinline__ void link_pass(const LaunchPart& a, int p, const Part
     ZAcc<Q> z;
     z.clear();
     constexpr int SEG_N = SEG / PBLOCK;
+    const bool held = nc <= KLINK * PBLOCK && running <= lcap;  // every node's mask is still in a register
     int c0 = 0;  // first link of the segment
     for (int g0 = 0; g0 < nsites && c0 < running; g0 += SEG) {
         const int nseg = sh.segcnt[g0 / SEG];
@@ -1835,7 +1880,12 @@ __device__ __forceinline__ void link_pass(const LaunchPart& a, int p, const Part
         __syncthreads();  // the stage, or the previous segment's masks, have been read; L is written
         for (int k = tid; k < SEG; k += PBLOCK) stage[k] = 0u;
         __syncthreads();
-        const int c1 = min(c0 + nseg, lcap);
+        if (held) {
+#pragma unroll
+            for (int c = 0; c < KLINK; ++c)
+                if (lmv[c] && (unsigned)(ni_[c] - g0) < (unsigned)SEG) stage[ni_[c] - g0] = lmv[c];
+        }
+        const int c1 = held ? 0 : min(c0 + nseg, lcap);
         for (int j = c0 + tid; j < c1; j += PBLOCK) {
             const uint32_t code = L[j];
             int x, y;
@@ -2036,8 +2086,7 @@ __global__ __launch_bounds__(PBLOCK) void k_particle_claim(LaunchPart a) {
 //    added particle's nodes.
 // At most 128 VGPRs (four waves per SIMD): two work-groups per compute unit,
 // so that the rebuilding work-groups of a large suspension are not queued
-// behind one another (five values spill: six scratch stores and four
-// reloads per thread, none in a loop).
+// behind one another.
 template <int Q>
 __global__ __launch_bounds__(PBLOCK, 4) void k_particle_links(LaunchPart a) {
     extern __shared__ uint32_t smem[];

@@ -144,11 +144,12 @@ size_t lb_arena_bytes(const lb_config* cfg, int nboxes, const lb_box* boxes);
  * f_eq(rho0, u0) with u0 = 0, or the wall-driven Couette profile (init = 1),
  * including its first-order non-equilibrium part.  Environment variables
  * read here: LBELL_K1_VARIANT picks the initial collide-stream variant (see
- * lb_autotune; by default it follows from the size of the populations); LBELL_FUSED=0 runs boxes that hold one particle through the
- * three-kernel particle phase as well; LBELL_BAND=0 makes every remap rescan
- * test the particle's whole window (by default a rescan between full tests
- * tests only the nodes the last full test found within one node of the
- * surface; the results are the same); LBELL_OVERLAP=1 selects the
+ * lb_autotune; by default it follows from the size of the populations);
+ * LBELL_FUSED=0 runs boxes that hold one particle through the three-kernel
+ * particle phase as well; LBELL_BAND=0 makes every remap rescan test the
+ * particle's whole window (by default a rescan between full tests tests only
+ * the nodes the last full test found within one node of the surface; the
+ * results are the same); LBELL_OVERLAP=1 selects the
  * two-stream schedule.  Synchronises the stream. */
 lb_status lb_init(const lb_config* cfg, int nboxes, const lb_box* boxes,
                   void* dev_arena, size_t arena_bytes, void* hip_stream,

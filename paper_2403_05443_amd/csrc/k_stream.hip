@@ -235,6 +235,9 @@ __device__ __forceinline__ void collide(R (&f)[Q], R rho0, R om, R omm, bool cf,
 // a small box's launch is a chain of dependent loads, and this takes two of
 // them (the tile's box, its description) from the front.  With the particle
 // kernel's two: a step of a 32^3 FP64 box 15.9 -> 14.8 us, of 128^3 FP32 59.9 -> 58.9.
+// Periodic boxes only: with walls the argument's wall velocities stay in registers
+// next to every direction (FP16 in variant 3: 54 -> 74 VGPRs), and the step was the
+// slower one at every size: 128^3 FP16 42.3 -> 47.7 us, 48^3 FP64 16.6 -> 17.1.
 template <int ST, int COLL, bool WALLS, bool NT, int CIN, int COUT, int Q, bool ONE>
 __device__ __forceinline__ void site_update(const BoxDesc* __restrict__ boxes, const int* __restrict__ tile_box,
                                             const BoxDesc& one, const typename Store<ST>::T* fin,
@@ -844,9 +847,10 @@ template <int ST, int COLL, bool WALLS, int Q>
 static hipError_t cs_shape(const LaunchCS& a, hipStream_t st) {
     const int key = a.spt * 8 + a.xcd * 2 + (a.nt ? 1 : 0);  // xcd: 0 plain, 1 chunked, 2 grouped
     // one box: the chunked shapes that small and medium boxes start with
-    if (key == 10 && a.one_box && a.part == 0)
-        return a.aa ? aa_one<ST, COLL, WALLS, 1, 1, false, Q, true>(a, st)
-                    : cs_one<ST, COLL, WALLS, 1, 1, false, Q, true>(a, st);
+    if constexpr (!WALLS)
+        if (key == 10 && a.one_box && a.part == 0)
+            return a.aa ? aa_one<ST, COLL, WALLS, 1, 1, false, Q, true>(a, st)
+                        : cs_one<ST, COLL, WALLS, 1, 1, false, Q, true>(a, st);
     if constexpr (Q == 27) {
         if (a.part != 0) return hipErrorInvalidValue;
         switch (key) {

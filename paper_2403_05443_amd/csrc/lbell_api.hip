@@ -9,6 +9,7 @@
 #include <string>
 #include <vector>
 
+#include "initial_variant.h"
 #include "lbell.h"
 #include "lbell_dev.h"
 #include "lbell_launch.h"
@@ -269,31 +270,12 @@ bool k1_applicable(const lb_ctx* ctx, int v) {
     return true;
 }
 
-// The variant a context starts with (all give the same bits; lb_autotune
-// measures them), by what one buffer of populations takes.  The times are per launch in
-// real steps, in us.
-//  - Two buffers fit the 256 MB last-level cache: pull, XCD-chunked (3): each
-//    XCD's L2 serves the cache lines its neighbouring tiles share.  96^3 FP32
-//    (67 MB) 18.2 against 19.2 in plain order (0) and 18.7 in place (12); 110^3 FP16 15.8,
-//    17.8, 16.9; 16 boxes of edges 32-64 in FP16 (74 MB) 21.3, 23.9, 22.0.
-//  - One buffer is worth keeping there: in place, XCD-chunked (12).  128^3
-//    FP32 (159 MB) 39 against 57 (0) and 59 (row-wave), 128^3 FP32 D3Q27 (226 MB) 55
-//    against 90, 160^3 FP16 (156 MB) 41 against 55; beyond the cache's size a share of
-//    it still hits: 160^3 FP32 (311 MB) 103 against 116 (15), 128^3 FP64
-//    (319 MB) 97 against 123.  At 442-453 MB (D3Q27) the two are level, at 538 MB
-//    pull wins, 191 against 212.  In the half formats it wins sooner, 192^3
-//    (269 MB) 94 against 107: the scattered stores are two bytes a lane.
-//  - Larger: pull in XCD-grouped order, non-temporal stores (15), 256^3 FP16 215 against 228
-//    (0) and 237 (row-wave), 256 boxes in FP16 368 against 382 (0); D3Q27 has
-//    no such kernel and takes the plain order (675 against 696 chunked, 256^3 FP32).
-// The two-stream schedule needs the plain order or the row-wave kernel.
-int initial_variant(const lb_ctx* ctx) {
+// The variant a context starts with; the two-stream schedule needs the plain
+// order or the row-wave kernel.
+int first_variant(const lb_ctx* ctx) {
     if (ctx->overlap) return ctx->rows_k > 0 ? 1 : 0;
     const int es = storage_bytes(ctx->cfg.storage);
-    const double mb = (double)ctx->L.pop_elems * es / 1e6;
-    if (2 * mb <= 256) return 3;
-    if (mb <= (es == 2 ? 200 : 400)) return 12;
-    return ctx->cfg.lattice == 27 ? 0 : 15;
+    return initial_variant(ctx->cfg.lattice, es, (double)ctx->L.pop_elems * es / 1e6, ctx->rows_k, ctx->any_walls);
 }
 
 lb_status fail(lb_ctx* c, lb_status s, const std::string& msg) {
@@ -504,7 +486,8 @@ lb_status lb_init(const lb_config* cfg, int nboxes, const lb_box* boxes, void* d
     if (const char* v = std::getenv("LBELL_OVERLAP")) ctx->overlap = std::atoi(v) != 0;
     if (const char* v = std::getenv("LBELL_FUSED")) ctx->fused = std::atoi(v) != 0;
     if (const char* v = std::getenv("LBELL_BAND")) ctx->use_band = std::atoi(v) != 0;
-    ctx->k1_variant = initial_variant(ctx);
+    for (int b = 0; b < nboxes; ++b) ctx->any_walls = ctx->any_walls || boxes[b].walls;
+    ctx->k1_variant = first_variant(ctx);
     if (const char* v = std::getenv("LBELL_K1_VARIANT")) {
         if (!k1_applicable(ctx, std::atoi(v))) {
             std::fprintf(stderr, "lb_init: LBELL_K1_VARIANT=%s does not apply to these boxes\n", v);
@@ -548,7 +531,6 @@ lb_status lb_init(const lb_config* cfg, int nboxes, const lb_box* boxes, void* d
         }
         for (int t = 0; t < D.ntiles; ++t) tile_box[D.tile0 + t] = b;
         init[b] = X.init;
-        ctx->any_walls = ctx->any_walls || X.walls;
     }
     // node map: walls 0xFFFF, everything else fluid
     std::vector<uint16_t> om((size_t)ctx->L.omap_elems, 0);

@@ -638,14 +638,15 @@ __device__ __forceinline__ double wave_sum8(const double (&v)[8], int lane) {
 // units).
 constexpr int YT = 128;  // rows of the phase table held in LDS at a time
 __global__ __launch_bounds__(256) void k_stokes_modes(const BoxDesc* __restrict__ boxes,
+                                                      const int* __restrict__ slab_box,
                                                       const double* __restrict__ uf, long long base, int only_box,
-                                                      int box_slabs, double* __restrict__ S) {
+                                                      double* __restrict__ S) {
     __shared__ double Bs[(2 * WK + 1) * UF][257];  // odd rows: the x sum reads a column of them
     __shared__ double ty[YT][4], tx[256][4];  // (cos, sin) of n = 1 and of n = 2
-    const int bi = blockIdx.x / box_slabs, slab = blockIdx.x % box_slabs, tid = threadIdx.x;
+    const int bi = slab_box[blockIdx.x], tid = threadIdx.x;
     if (only_box >= 0 && bi != only_box) return;  // uniform over the block
     const BoxDesc& B = boxes[bi];
-    if (slab >= B.nslab) return;  // uniform over the block
+    const int slab = (int)blockIdx.x - B.slab0;
     const int nx = B.nx, ny = B.ny, nz = B.nz;
     auto phase = [](double (&t)[4], int i, int n) {
         double c, s;
@@ -1246,7 +1247,7 @@ size_t stokes_scratch_doubles(int nboxes, int ntiles, int nslabs, int max_partic
 int stokes_free_doubles() { return UF; }
 
 hipError_t launch_stokes_start(const BoxDesc* boxes, int nboxes, const int* tile_box, int ntiles, int nslabs,
-                               int box_slabs, int rows, int planes, int max_particles, const uint16_t* omap,
+                               const int* slab_box, int rows, int planes, int max_particles, const uint16_t* omap,
                                const PartDev* parts, int np, double mu, double* scratch, double* uf, long long base,
                                void* f, const KParams& kp, int only_box, hipStream_t st) {
     const StokesScratch L = stokes_layout(nboxes, ntiles, nslabs, max_particles);
@@ -1257,8 +1258,7 @@ hipError_t launch_stokes_start(const BoxDesc* boxes, int nboxes, const int* tile
         hipLaunchKernelGGL(k_stokes_prep, dim3((np + 63) / 64), dim3(64), 0, st, parts, np, mu, fc, pbox);
     hipLaunchKernelGGL(k_stokes_free, dim3(ntiles), dim3(TILE), 0, st, boxes, tile_box, fc, pbox, np, only_box, base,
                        uf);
-    hipLaunchKernelGGL(k_stokes_modes, dim3(box_slabs * nboxes), dim3(256), 0, st, boxes, uf, base, only_box, box_slabs,
-                       S);
+    hipLaunchKernelGGL(k_stokes_modes, dim3(nslabs), dim3(256), 0, st, boxes, slab_box, uf, base, only_box, S);
     hipLaunchKernelGGL(k_stokes_coef, dim3(nboxes), dim3(128), 0, st, boxes, parts, pbox, np, mu, only_box, S, C);
     hipLaunchKernelGGL(k_stokes_sum, dim3(ntiles), dim3(TILE),
                        sizeof(double) * ((size_t)planes * PLANE_DOUBLES + (size_t)rows * ROW_DOUBLES), st, boxes,

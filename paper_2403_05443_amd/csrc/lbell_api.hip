@@ -32,7 +32,7 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 struct Layout {
     size_t f0 = 0, f1 = 0, omap = 0, boxes = 0, rt = 0, tile_box = 0, box_init = 0, parts = 0, links = 0,
            flags = 0, scratch = 0, near_flags = 0, near_list = 0, near_count = 0, warm = 0, step_ctr = 0,
-           stamps = 0, cand = 0, band = 0, mon = 0, total = 0;
+           stamps = 0, cand = 0, band = 0, mon = 0, slab_box = 0, total = 0;
     long long cells = 0;  // owner-change stamp cells over all boxes
     int near_blocks = 0;  // collide-stream blocks that a near set can name (per slot)
     std::vector<long long> foff, stride, ooff, coff;
@@ -40,7 +40,7 @@ struct Layout {
     long long pop_elems = 0, omap_elems = 0, link_pool = 0;
     int total_tiles = 0, max_particles = 0, lds_words = 0;
     std::vector<int> slab0, nslab;
-    int total_slabs = 0, box_slabs = 0;  // of the start field's Fourier sums: over all boxes, the largest of one
+    int total_slabs = 0;  // of the start field's Fourier sums, over all boxes
     int tile_rows = 0, tile_planes = 0;  // rows and planes a 256-site tile can touch
     size_t scratch_bytes = 0;
 };
@@ -112,7 +112,6 @@ Layout make_layout(const lb_config* c, int nboxes, const lb_box* boxes) {
         L.slab0.push_back(L.total_slabs);
         L.nslab.push_back(stokes_slabs(boxes[b].nx, boxes[b].ny, boxes[b].nz));
         L.total_slabs += L.nslab[b];
-        L.box_slabs = std::max(L.box_slabs, L.nslab[b]);
         stokes_tile(boxes[b].nx, boxes[b].ny, L.tile_rows, L.tile_planes);
         maxpart = std::max(maxpart, (size_t)((n + TILE - 1) / TILE) * 6 * sizeof(double));
         L.coff.push_back(L.cells);
@@ -164,6 +163,7 @@ Layout make_layout(const lb_config* c, int nboxes, const lb_box* boxes) {
     // warm-start monitor: a record per box, each particle's velocity at the
     // last check (6 doubles), a flow-energy partial per tile
     L.mon = take(sizeof(BoxMon) * nboxes + sizeof(double) * (6 * (size_t)L.max_particles + tiles));
+    L.slab_box = take(sizeof(int) * L.total_slabs);
     L.total = p;
     return L;
 }
@@ -501,7 +501,7 @@ lb_status lb_init(const lb_config* cfg, int nboxes, const lb_box* boxes, void* d
     ctx->set_cur(ctx->aa ? 1 : 0);
     // box descriptors and tile table
     ctx->hbox.resize(nboxes);
-    std::vector<int> tile_box(ctx->L.total_tiles), init(nboxes);
+    std::vector<int> tile_box(ctx->L.total_tiles), slab_box(ctx->L.total_slabs), init(nboxes);
     for (int b = 0; b < nboxes; ++b) {
         BoxDesc& D = ctx->hbox[b];
         std::memset(&D, 0, sizeof D);
@@ -530,6 +530,7 @@ lb_status lb_init(const lb_config* cfg, int nboxes, const lb_box* boxes, void* d
             D.wall_hi[k] = X.wall_hi[k];
         }
         for (int t = 0; t < D.ntiles; ++t) tile_box[D.tile0 + t] = b;
+        for (int h = 0; h < D.nslab; ++h) slab_box[D.slab0 + h] = b;
         init[b] = X.init;
     }
     // node map: walls 0xFFFF, everything else fluid
@@ -554,6 +555,8 @@ lb_status lb_init(const lb_config* cfg, int nboxes, const lb_box* boxes, void* d
     H(hipMemcpyAsync(ctx->at<BoxRT>(ctx->L.rt), rt.data(), sizeof(BoxRT) * nboxes, hipMemcpyHostToDevice,
                      ctx->stream));
     H(hipMemcpyAsync(ctx->at<int>(ctx->L.tile_box), tile_box.data(), sizeof(int) * tile_box.size(),
+                     hipMemcpyHostToDevice, ctx->stream));
+    H(hipMemcpyAsync(ctx->at<int>(ctx->L.slab_box), slab_box.data(), sizeof(int) * slab_box.size(),
                      hipMemcpyHostToDevice, ctx->stream));
     H(hipMemcpyAsync(ctx->at<int>(ctx->L.box_init), init.data(), sizeof(int) * nboxes, hipMemcpyHostToDevice,
                      ctx->stream));
@@ -1425,8 +1428,8 @@ lb_status stokes_start(lb_ctx* ctx, int only_box = -1) {
         return fail(ctx, LB_EINVAL, "population buffer too small for the start field's scratch");
     }
     HIPC(launch_stokes_start(ctx->at<BoxDesc>(ctx->L.boxes), (int)ctx->boxes.size(), ctx->at<int>(ctx->L.tile_box),
-                             ctx->L.total_tiles, ctx->L.total_slabs, ctx->L.box_slabs, ctx->L.tile_rows,
-                             ctx->L.tile_planes, ctx->L.max_particles,
+                             ctx->L.total_tiles, ctx->L.total_slabs, ctx->at<int>(ctx->L.slab_box),
+                             ctx->L.tile_rows, ctx->L.tile_planes, ctx->L.max_particles,
                              ctx->at<uint16_t>(ctx->L.omap), ctx->at<PartDev>(ctx->L.parts), ctx->np,
                              viscosity(ctx) * ctx->kp.rho0, scratch, (double*)spare, base, ctx->fbuf(ctx->cur),
                              ctx->kp, only_box, ctx->stream));

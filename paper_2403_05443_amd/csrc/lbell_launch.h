@@ -143,13 +143,12 @@ int stokes_slabs(int nx, int ny, int nz);  // work-groups (and partial sums) of 
 void stokes_tile(int nx, int ny, int& rows, int& planes);
 size_t stokes_scratch_doubles(int nboxes, int ntiles, int nslabs, int max_particles);  // scratch of launch_stokes_start
 int stokes_free_doubles();  // doubles per node of its staged free field (uf)
-// nslabs: over all boxes; box_slabs: the largest of one box; rows, planes: of
-// stokes_tile over the boxes.  only_box >= 0:
-// that box only (every box otherwise).  uf: stokes_free_doubles() doubles per
+// nslabs: over all boxes, slab_box the box of each; rows, planes: of stokes_tile
+// over the boxes.  only_box >= 0: that box only (every box otherwise).  uf: stokes_free_doubles() doubles per
 // node of the started boxes (16-byte aligned), node (box B, site s) at that many
 // times (B.ooff + s - base).
 hipError_t launch_stokes_start(const BoxDesc* boxes, int nboxes, const int* tile_box, int ntiles, int nslabs,
-                               int box_slabs, int rows, int planes, int max_particles, const uint16_t* omap,
+                               const int* slab_box, int rows, int planes, int max_particles, const uint16_t* omap,
                                const PartDev* parts, int np, double mu, double* scratch, double* uf, long long base,
                                void* f, const KParams& kp, int only_box, hipStream_t st);
 // ---- fallback monitor of warm-started boxes ----

@@ -1196,17 +1196,20 @@ lb_status lb_get_fields(lb_ctx* ctx, int box, double* rho, double* u) {
     double* tmp = ctx->at<double>(ctx->L.scratch);
     // each chunk straight into the caller's arrays (a copy to a host buffer and a
     // loop over its sites took most of the call: 64 x 128 x 64 sites 3.4 -> 1.4 ms)
-    for (int s0 = 0; s0 < B.n; s0 += FIELDS_CHUNK) {
+    hipError_t e = hipSuccess;
+    for (int s0 = 0; s0 < B.n && e == hipSuccess; s0 += FIELDS_CHUNK) {
         const int cnt = std::min(FIELDS_CHUNK, B.n - s0);
-        HIPC(launch_fields(ctx->at<BoxDesc>(ctx->L.boxes), box, ctx->at<uint16_t>(ctx->L.omap), ctx->fbuf(ctx->cur),
-                           s0, cnt, tmp, ctx->kp, ctx->stream));
-        if (rho) HIPC(hipMemcpyAsync(rho + s0, tmp, sizeof(double) * cnt, hipMemcpyDeviceToHost, ctx->stream));
-        if (u)
-            HIPC(hipMemcpyAsync(u + 3 * (size_t)s0, tmp + cnt, sizeof(double) * 3 * cnt, hipMemcpyDeviceToHost,
-                                ctx->stream));
+        e = launch_fields(ctx->at<BoxDesc>(ctx->L.boxes), box, ctx->at<uint16_t>(ctx->L.omap), ctx->fbuf(ctx->cur), s0,
+                          cnt, tmp, ctx->kp, ctx->stream);
+        if (rho && e == hipSuccess)
+            e = hipMemcpyAsync(rho + s0, tmp, sizeof(double) * cnt, hipMemcpyDeviceToHost, ctx->stream);
+        if (u && e == hipSuccess)
+            e = hipMemcpyAsync(u + 3 * (size_t)s0, tmp + cnt, sizeof(double) * 3 * cnt, hipMemcpyDeviceToHost,
+                               ctx->stream);
     }
-    HIPC(hipStreamSynchronize(ctx->stream));
-    return LB_OK;
+    // also after an error: no copy into the caller's arrays outlives the call
+    const hipError_t done = hipStreamSynchronize(ctx->stream);
+    return hip_check(ctx, e != hipSuccess ? e : done, "field read-back");
 }
 
 lb_status lb_get_mass(lb_ctx* ctx, int box, double* mass) {

@@ -136,7 +136,8 @@ Layout make_layout(const lb_config* c, int nboxes, const lb_box* boxes) {
     L.boxes = take(sizeof(BoxDesc) * nboxes);
     L.rt = take(sizeof(BoxRT) * nboxes);
     L.tile_box = take(sizeof(int) * tiles);
-    L.box_init = take(sizeof(int) * nboxes);
+    L.box_init = take(sizeof(int) * (nboxes + (size_t)L.total_slabs));
+    L.slab_box = L.box_init + sizeof(int) * nboxes;  // one copy at set-up fills both
     L.parts = take(sizeof(PartDev) * L.max_particles);
     L.links = take(sizeof(uint32_t) * L.link_pool);
     L.flags = take(sizeof(int) * 4);
@@ -163,7 +164,6 @@ Layout make_layout(const lb_config* c, int nboxes, const lb_box* boxes) {
     // warm-start monitor: a record per box, each particle's velocity at the
     // last check (6 doubles), a flow-energy partial per tile
     L.mon = take(sizeof(BoxMon) * nboxes + sizeof(double) * (6 * (size_t)L.max_particles + tiles));
-    L.slab_box = take(sizeof(int) * L.total_slabs);
     L.total = p;
     return L;
 }
@@ -501,7 +501,7 @@ lb_status lb_init(const lb_config* cfg, int nboxes, const lb_box* boxes, void* d
     ctx->set_cur(ctx->aa ? 1 : 0);
     // box descriptors and tile table
     ctx->hbox.resize(nboxes);
-    std::vector<int> tile_box(ctx->L.total_tiles), slab_box(ctx->L.total_slabs), init(nboxes);
+    std::vector<int> tile_box(ctx->L.total_tiles), init(nboxes + (size_t)ctx->L.total_slabs);
     for (int b = 0; b < nboxes; ++b) {
         BoxDesc& D = ctx->hbox[b];
         std::memset(&D, 0, sizeof D);
@@ -530,7 +530,7 @@ lb_status lb_init(const lb_config* cfg, int nboxes, const lb_box* boxes, void* d
             D.wall_hi[k] = X.wall_hi[k];
         }
         for (int t = 0; t < D.ntiles; ++t) tile_box[D.tile0 + t] = b;
-        for (int h = 0; h < D.nslab; ++h) slab_box[D.slab0 + h] = b;
+        for (int h = 0; h < D.nslab; ++h) init[nboxes + (size_t)D.slab0 + h] = b;
         init[b] = X.init;
     }
     // node map: walls 0xFFFF, everything else fluid
@@ -556,9 +556,7 @@ lb_status lb_init(const lb_config* cfg, int nboxes, const lb_box* boxes, void* d
                      ctx->stream));
     H(hipMemcpyAsync(ctx->at<int>(ctx->L.tile_box), tile_box.data(), sizeof(int) * tile_box.size(),
                      hipMemcpyHostToDevice, ctx->stream));
-    H(hipMemcpyAsync(ctx->at<int>(ctx->L.slab_box), slab_box.data(), sizeof(int) * slab_box.size(),
-                     hipMemcpyHostToDevice, ctx->stream));
-    H(hipMemcpyAsync(ctx->at<int>(ctx->L.box_init), init.data(), sizeof(int) * nboxes, hipMemcpyHostToDevice,
+    H(hipMemcpyAsync(ctx->at<int>(ctx->L.box_init), init.data(), sizeof(int) * init.size(), hipMemcpyHostToDevice,
                      ctx->stream));
     H(hipMemcpyAsync(ctx->at<uint16_t>(ctx->L.omap), om.data(), sizeof(uint16_t) * om.size(), hipMemcpyHostToDevice,
                      ctx->stream));

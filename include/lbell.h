@@ -144,7 +144,7 @@ size_t lb_arena_bytes(const lb_config* cfg, int nboxes, const lb_box* boxes);
  * f_eq(rho0, u0) with u0 = 0, or the wall-driven Couette profile (init = 1),
  * including its first-order non-equilibrium part.  Environment variables
  * read here: LBELL_K1_VARIANT picks the initial collide-stream variant (see
- * lb_autotune; by default it follows from the size of the populations);
+ * lb_autotune; by default it follows from the sizes, storage and walls);
  * LBELL_FUSED=0 runs boxes that hold one particle through the three-kernel
  * particle phase as well; LBELL_BAND=0 makes every remap rescan test the
  * particle's whole window (by default a rescan between full tests tests only

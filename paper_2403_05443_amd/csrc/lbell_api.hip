@@ -1423,7 +1423,7 @@ lb_status stokes_start(lb_ctx* ctx, int only_box = -1) {
         const BoxDesc& B = ctx->hbox[only_box];
         if ((size_t)B.n * need > (size_t)ctx->cfg.lattice * B.stride * es)
             return fail(ctx, LB_EINVAL, "population block too small for the start field's scratch");
-        spare += (size_t)B.foff * es;  // foff is a multiple of 128 elements: 8-byte aligned
+        spare += (size_t)B.foff * es;  // foff is a multiple of 128 elements: 256-byte aligned (the kernels need 16)
         base = B.ooff;
     } else if ((size_t)ctx->L.omap_elems * need > (size_t)ctx->L.pop_elems * es) {
         return fail(ctx, LB_EINVAL, "population buffer too small for the start field's scratch");

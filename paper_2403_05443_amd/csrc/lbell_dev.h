@@ -254,7 +254,6 @@ namespace lbd {
 // Population storage formats (values of lb_config.storage).
 constexpr int ST_F64 = 0, ST_F32 = 1, ST_F16 = 2, ST_BF16 = 3;
 
-// Stored value <-> deviation f_i - w_i rho0 in the collision precision R.
 // Nearest half (ties to even) of a double.  Rounded first to odd at float's 24
 // bits (the 29 below them folded into the last one kept), which the second
 // rounding to half's 11 cannot tell from the exact value.  gfx950 has no
@@ -270,6 +269,7 @@ __device__ __forceinline__ _Float16 f64_to_f16(double v) {
     return (_Float16)f;
 }
 
+// Stored value <-> deviation f_i - w_i rho0 in the collision precision R.
 template <int ST> struct Store;
 template <> struct Store<ST_F64> {
     using T = double;
